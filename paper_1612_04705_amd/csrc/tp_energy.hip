@@ -69,6 +69,8 @@ constexpr int ROWS = 128;     // rows i per workgroup (4 waves x 32)
 constexpr int JC = 128;       // j per LDS chunk
 constexpr int KS = 16;        // j per matrix-core step
 constexpr int FL = 8;         // chunks per float32 -> float64 reduction
+constexpr int WG_MIN = 512;   // workgroups of a launch (see launch_ntd)
+constexpr int WG_MAX = 8192;
 constexpr int GPAD = 8;       // float16 padding per staged column (spreads LDS banks)
 constexpr int XS = 40;        // float16 slots per staged j vector: 32 used, 8 padding (spreads LDS banks)
 constexpr float PSI_LOG2 = 14.0f;             // psi is formed scaled by 2^14
@@ -84,9 +86,10 @@ struct Smem {
     uint16_t xh[JC][XS];                // chunk j distance operands, float16 slots (see slot())
     float cw[4][MAXD];                  // per-wave coordinate sums for the centre c
     float cen[MAXD];                    // the centre c
-    uint16_t gs[C][JC + GPAD];          // columns of the chunk, [c][j], float16 0 or 1
-    uint8_t gi[ROWS * C];               // columns of this block's rows, [i][c]
-    float rw[ROWS][8];                  // per row: weights G[i][q] (0..2), (Psi_upper G)[i][q] (4..6)
+    union {
+        uint16_t gs[C][JC + GPAD];      // columns of the chunk, [c][j], float16 0 or 1
+        uint8_t gi[ROWS * C];           // row block set-up only: columns of the block's rows, [i][c]
+    };
     double red[C][1 + MAXR];            // workgroup totals
     // SAFE: raw coordinates of the block's rows and of the chunk's events (direct distances)
     float yr[SAFE ? ROWS : 1][MAXD + 1];
@@ -150,19 +153,32 @@ __device__ __forceinline__ void split16(const float (&x)[KA], uint16_t (&hi)[KA]
     }
 }
 
-// Row block setup: columns and row weights of rows ib .. ib + ROWS - 1, and
-// this lane's operand halves of its row's vector x_i = (-2 (y_i - c), 1,
+// What a lane keeps of its wave's 32 rows for the flush: bit r of g[t] is the
+// column value G[row][32 t + col], bit r of w[q] the row weight G[row][q], row =
+// 8 (r / 4) + 4 h + r % 4 (the lane's rows in a product tile).
+template <int NT, int RR>
+struct RowBits {
+    uint32_t g[NT];
+    uint32_t w[RR];
+};
+
+// Row block setup: column and weight bits of rows ib .. ib + ROWS - 1 (staged
+// through LDS once, in the space of the chunk's columns, and kept in registers),
+// and this lane's operand halves of its row's vector x_i = (-2 (y_i - c), 1,
 // |y_i - c|^2) (scaled coordinates, so psi = 2^-(scaled distance)^2):
 // x_i . x_j = |y_i - y_j|^2 for the chunk vectors x_j.  Lane half h holds
 // slots 16 m + 8 h .. + 7 of the row pattern for the two distance steps m.
-template <int NT, int NS, bool SAFE>
-__device__ __forceinline__ bool setup_rows(const EParams &p, Smem<NT, SAFE> &sm, int64_t ib, u32x4 (&xi)[2])
+// The caller's next write of the chunk's columns follows a barrier.
+template <int NT, int NS, int RR, bool SAFE>
+__device__ __forceinline__ bool setup_rows(const EParams &p, Smem<NT, SAFE> &sm, int64_t ib, u32x4 (&xi)[2],
+                                           RowBits<NT, RR> &rb)
 {
     constexpr int C = 32 * NT;
     constexpr int KA = 2 * NS;
     const int tid = threadIdx.x;
     const int h = (tid >> 5) & 1;
-    const int64_t i = ib + (tid >> 6) * 32 + (tid & 31);
+    const int col = tid & 31;
+    const int64_t i = ib + (tid >> 6) * 32 + col;
     __syncthreads();
     for (int e = tid; e < ROWS * C / 16; e += 256) {
         const int64_t r = ib + (e * 16) / C;
@@ -170,19 +186,11 @@ __device__ __forceinline__ bool setup_rows(const EParams &p, Smem<NT, SAFE> &sm,
         if (r < p.n) w = reinterpret_cast<const u32x4 *>(p.G + ib * C)[e];
         reinterpret_cast<u32x4 *>(sm.gi)[e] = w;
     }
-    if (tid < ROWS) {
-        const int64_t r = ib + tid;
-#pragma unroll
-        for (int q = 0; q < MAXR; ++q)
-            sm.rw[tid][q] = (q < p.R && r < p.n) ? (float)p.G[r * C + q] : 0.0f;
-#pragma unroll
-        for (int q = 3; q < 8; ++q) sm.rw[tid][q] = 0.0f;
-    }
     float x[KA];
     float nrm = 0.0f;
 #pragma unroll
     for (int k = 0; k < KA; ++k) x[k] = 0.0f;
-    const int rl = (tid >> 6) * 32 + (tid & 31);
+    const int rl = (tid >> 6) * 32 + col;
 #pragma unroll
     for (int d = 0; d < KA - 2; ++d) {
         const float y = (d < p.D && i < p.n) ? p.Y[d * p.ldY + i] : 0.0f;
@@ -214,8 +222,22 @@ __device__ __forceinline__ bool setup_rows(const EParams &p, Smem<NT, SAFE> &sm,
             const int s0 = 16 * m + 8 * h + 2 * w;
             xi[m][w] = (uint32_t)slot<KA, false>(hi, lo, s0) | ((uint32_t)slot<KA, false>(hi, lo, s0 + 1) << 16);
         }
-    if constexpr (SAFE) return __syncthreads_or(far) != 0;
-    return false;
+    bool any = false;
+    if constexpr (SAFE) any = __syncthreads_or(far) != 0;
+    else __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t) rb.g[t] = 0u;
+#pragma unroll
+    for (int q = 0; q < RR; ++q) rb.w[q] = 0u;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const uint8_t *row = sm.gi + ((tid >> 6) * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * C;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) rb.g[t] |= (uint32_t)row[32 * t + col] << r;
+#pragma unroll
+        for (int q = 0; q < RR; ++q) rb.w[q] |= (q < p.R ? (uint32_t)row[q] : 0u) << r;
+    }
+    return any;
 }
 
 // Position of local j in a staged column: bits 2 and 3 swapped, the order in
@@ -402,39 +424,31 @@ __device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, const u
 // Reduce the float32 tiles into the float64 partials and clear them.  Lane
 // (col, h) holds column 32 t + col for rows 8 (r / 4) + 4 h + r % 4 of its
 // wave's 32.  The leading R columns are the row weights; their values
-// (Psi_upper w_q)_i go through LDS so that every column can take the
-// transposed term sum_i G_ic (Psi_upper w_q)_i.
-template <int NT, int RR, bool SAFE>
-__device__ __forceinline__ void flush(const EParams &p, Smem<NT, SAFE> &sm, f32x16 (&acc)[NT],
-                                      double (&part)[NT][1 + RR])
+// (Psi_upper w_q)_i come from the lane that holds them (lane q of the half), so
+// that every column can take the transposed term sum_i G_ic (Psi_upper w_q)_i.
+template <int NT, int RR>
+__device__ __forceinline__ void flush(const RowBits<NT, RR> &rb, f32x16 (&acc)[NT], double (&part)[NT][1 + RR])
 {
-    constexpr int C = 32 * NT;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int h = lane >> 5;
-    const int col = lane & 31;
-    if (col < p.R) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sm.rw[wave * 32 + 8 * (r >> 2) + 4 * h + (r & 3)][4 + col] = acc[0][r];
-    }
-    __syncthreads();
+    const int src = threadIdx.x & 32;
     float s0[NT], s1[NT], s2[NT], s3[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) s0[t] = s1[t] = s2[t] = s3[t] = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int row = wave * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-        const f32x4 wq = reinterpret_cast<const f32x4 *>(&sm.rw[row][0])[0];
-        const f32x4 vq = reinterpret_cast<const f32x4 *>(&sm.rw[row][0])[1];
+        float w[RR], u[RR];
+#pragma unroll
+        for (int q = 0; q < RR; ++q) {
+            w[q] = (float)((rb.w[q] >> r) & 1u);
+            u[q] = __shfl(acc[0][r], src + q);
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const float v = acc[t][r];
-            const float g = (float)sm.gi[row * C + 32 * t + col];
+            const float g = (float)((rb.g[t] >> r) & 1u);
             s0[t] = fmaf(g, v, s0[t]);
-            s1[t] = fmaf(wq.x, v, fmaf(g, vq.x, s1[t]));
-            if (RR > 1) s2[t] = fmaf(wq.y, v, fmaf(g, vq.y, s2[t]));
-            if (RR > 2) s3[t] = fmaf(wq.z, v, fmaf(g, vq.z, s3[t]));
+            s1[t] = fmaf(w[0], v, fmaf(g, u[0], s1[t]));
+            if constexpr (RR > 1) s2[t] = fmaf(w[1], v, fmaf(g, u[1], s2[t]));
+            if constexpr (RR > 2) s3[t] = fmaf(w[2], v, fmaf(g, u[2], s3[t]));
         }
     }
 #pragma unroll
@@ -447,13 +461,53 @@ __device__ __forceinline__ void flush(const EParams &p, Smem<NT, SAFE> &sm, f32x
     }
 }
 
-// Work split.  Row blocks g and nb - 1 - g pair up (together about n pairs per
-// row); their chunks, block g's first, form one list that K workgroups share in
-// equal contiguous pieces, so the launch has enough equal-sized workgroups to
-// keep every compute unit busy to the end.
+// Work split.  Row blocks g and nb - 1 - g pair up (together nb + 1 chunks);
+// their chunks, block g's first, form one list, and the lists of all pairs in
+// turn one sequence of chunks.  Float32 accumulation runs over segments of
+// this sequence: a pair's list is cut into K equal pieces, a piece at the row
+// block's end, and the rest every FL chunks.  Workgroups take equal contiguous
+// shares of the sequence, rounded to segments, so a share costs one set-up and
+// one reduction however small the pieces are, and the float32 sums do not
+// depend on how many workgroups there are.  (One workgroup per piece instead:
+// at 3e4 events pieces of two chunks, 13.8 k workgroups, each with its centre,
+// its rows' columns, and 256 float64 atomics on the same addresses as the
+// others': 0.533 ms against 0.353 ms, 128 columns; at 1e5 events with two row
+// weights 3.19 against 2.69 ms; at 1e6 events 264 against 253 ms, the last from
+// the flush reading its row columns from registers instead of LDS.)
+struct Seq {
+    int64_t n, nb;
+    int K;
+    __device__ __forceinline__ int64_t len1(int64_t g) const { return nb - g; }             // chunks of block g's row
+    __device__ __forceinline__ int64_t len(int64_t g) const                                  // of the pair's list
+    {
+        return 2 * g + 1 == nb ? nb - g : nb + 1;
+    }
+    // the segment of pair g that holds list position v: its first position, end
+    __device__ __forceinline__ void segment(int64_t g, int64_t v, int64_t &s0, int64_t &s1) const
+    {
+        const int64_t L1 = len1(g), L = len(g);
+        const int64_t k = ((v + 1) * K - 1) / L;
+        int64_t a = k * L / K, b = (k + 1) * L / K;
+        if (v < L1) b = b < L1 ? b : L1;
+        else a = a > L1 ? a : L1;
+        s0 = a + (v - a) / FL * FL;
+        s1 = s0 + FL < b ? s0 + FL : b;
+    }
+    // sequence position ``pos`` rounded down to a segment's start
+    __device__ __forceinline__ int64_t round(int64_t pos, int64_t total) const
+    {
+        if (pos >= total) return total;
+        const int64_t g = pos / (nb + 1), v = pos % (nb + 1);
+        int64_t s0, s1;
+        segment(g, v, s0, s1);
+        return pos - (v - s0);
+    }
+};
+
 // RR: row-weight columns the reduction carries (RR covers R <= RR).
 template <int NT, int NS, int RR, bool SAFE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void tp_pairsum_kernel(const EParams p, const int K)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void tp_pairsum_kernel(const EParams p, const int K,
+                                                                                                 const int64_t total)
 {
     constexpr int C = 32 * NT;
     // the range check's flag selects the one instantiation that works
@@ -465,76 +519,81 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
     const int wave = tid >> 6;
     const int h = lane >> 5;
     const int col = lane & 31;
-    const int64_t nb = (p.n + ROWS - 1) / ROWS;
-    for (int e = tid; e < C * (1 + MAXR); e += 256) (&sm.red[0][0])[e] = 0.0;
-    double part[NT][1 + RR];
+    const Seq sq = { p.n, (p.n + ROWS - 1) / ROWS, K };
+    // this workgroup's share [pos, end) of the sequence of chunks
+    const int64_t share = total / gridDim.x, extra = total % gridDim.x, wg = blockIdx.x;
+    int64_t pos = sq.round(wg * share + (wg < extra ? wg : extra), total);
+    const int64_t end = sq.round((wg + 1) * share + (wg + 1 < extra ? wg + 1 : extra), total);
+    const bool works = pos < end;
+    if (works) {
+        for (int e = tid; e < C * (1 + MAXR); e += 256) (&sm.red[0][0])[e] = 0.0;
+        double part[NT][1 + RR];
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int q = 0; q <= RR; ++q) part[t][q] = 0.0;
-    f32x16 acc[NT];
+            for (int q = 0; q <= RR; ++q) part[t][q] = 0.0;
+        f32x16 acc[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x16{};
-
-    const int64_t g = blockIdx.x / K, k = blockIdx.x % K;
-    const int64_t b1 = g, b2 = nb - 1 - g;
-    // ROWS == JC: a row block starts a chunk, and its first chunk holds the diagonal
-    const int64_t L1 = (p.n - b1 * ROWS + JC - 1) / JC;
-    const int64_t L2 = b2 > b1 ? (p.n - b2 * ROWS + JC - 1) / JC : 0;
-    const int64_t L = L1 + L2;
-    const int64_t v0 = k * L / K, v1 = (k + 1) * L / K;
-    centre(p, sm);
-    u32x4 xi[2];
-    int64_t cur = -1;
-    int since = 0;
-    // chunk v: row block b1 for v < L1 (chunk v of its row), else b2 (chunk v - L1)
-    auto chunk_j0 = [&](int64_t v) { return v < L1 ? b1 * ROWS + v * JC : b2 * ROWS + (v - L1) * JC; };
-    Pending<2 * NS> pd;
-    if (v0 < v1) load_chunk<NT, 2 * NS>(p, chunk_j0(v0), pd);
-    bool rows_far = false;
-    for (int64_t v = v0; v < v1; ++v) {
-        const int64_t blk = v < L1 ? b1 : b2;
-        const int64_t c0 = v < L1 ? v : v - L1;      // chunk within the block's row
-        const int64_t j0 = chunk_j0(v);
-        if (blk != cur) {
-            rows_far = setup_rows<NT, NS, SAFE>(p, sm, blk * ROWS, xi);
-            cur = blk;
+        for (int t = 0; t < NT; ++t) acc[t] = f32x16{};
+        centre(p, sm);
+        u32x4 xi[2];
+        RowBits<NT, RR> rb;
+        int64_t g = pos / (sq.nb + 1), v = pos % (sq.nb + 1), cur = -1;
+        // ROWS == JC: a row block starts a chunk, and its first chunk holds the diagonal
+        auto chunk_j0 = [&](int64_t gg, int64_t vv) {
+            const int64_t L1 = sq.len1(gg);
+            return (vv < L1 ? gg + vv : sq.nb - 1 - gg + (vv - L1)) * JC;
+        };
+        Pending<2 * NS> pd;
+        load_chunk<NT, 2 * NS>(p, chunk_j0(g, v), pd);
+        bool rows_far = false;
+        while (pos < end) {
+            const int64_t L1 = sq.len1(g), L = sq.len(g);
+            const int64_t blk = v < L1 ? g : sq.nb - 1 - g;
+            int64_t s0, s1;
+            sq.segment(g, v, s0, s1);
+            if (blk != cur) {
+                rows_far = setup_rows<NT, NS, RR, SAFE>(p, sm, blk * ROWS, xi, rb);
+                cur = blk;
+            }
+            for (; v < s1; ++v, ++pos) {
+                const int64_t c0 = v < L1 ? v : v - L1;      // chunk within the block's row
+                __syncthreads();
+                const bool cfar = store_chunk<NT, 2 * NS, SAFE>(p, sm, chunk_j0(g, v), pd);
+                bool far = false;
+                if constexpr (SAFE) far = __syncthreads_or(cfar) != 0 || rows_far;
+                else __syncthreads();
+                if (pos + 1 < end) load_chunk<NT, 2 * NS>(p, v + 1 < L ? chunk_j0(g, v + 1) : chunk_j0(g + 1, 0), pd);
+                if (SAFE && far) {    // uniform over the workgroup
+                    if (c0 == 0) chunk_products<NT, true, SAFE, SAFE>(sm, xi, wave * 32 + col, acc, p.D, p.yscale);
+                    else chunk_products<NT, false, SAFE, SAFE>(sm, xi, 0, acc, p.D, p.yscale);
+                } else {
+                    if (c0 == 0) chunk_products<NT, true, SAFE, false>(sm, xi, wave * 32 + col, acc, p.D, p.yscale);
+                    else chunk_products<NT, false, SAFE, false>(sm, xi, 0, acc, p.D, p.yscale);
+                }
+            }
+            flush<NT, RR>(rb, acc, part);
+            if (v == L) {
+                v = 0;
+                ++g;
+            }
         }
+        // combine the two row halves of each column, then the four waves, then workgroups
+        const int R = p.R;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int q = 0; q <= RR; ++q) {
+                double x = part[t][q];
+                x += __shfl_xor(x, 32);
+                if (h == 0 && q <= R) atomicAdd(&sm.red[32 * t + col][q], x);
+            }
         __syncthreads();
-        const bool cfar = store_chunk<NT, 2 * NS, SAFE>(p, sm, j0, pd);
-        bool far = false;
-        if constexpr (SAFE) far = __syncthreads_or(cfar) != 0 || rows_far;
-        else __syncthreads();
-        if (v + 1 < v1) load_chunk<NT, 2 * NS>(p, chunk_j0(v + 1), pd);
-        if (SAFE && far) {    // uniform over the workgroup
-            if (c0 == 0) chunk_products<NT, true, SAFE, SAFE>(sm, xi, wave * 32 + col, acc, p.D, p.yscale);
-            else chunk_products<NT, false, SAFE, SAFE>(sm, xi, 0, acc, p.D, p.yscale);
-        } else {
-            if (c0 == 0) chunk_products<NT, true, SAFE, false>(sm, xi, wave * 32 + col, acc, p.D, p.yscale);
-            else chunk_products<NT, false, SAFE, false>(sm, xi, 0, acc, p.D, p.yscale);
-        }
-        const bool block_ends = v + 1 == v1 || v + 1 == L1;
-        if (++since == FL || block_ends) {
-            flush<NT, RR, SAFE>(p, sm, acc, part);
-            since = 0;
-        }
-    }
-    // combine the two row halves of each column, then the four waves, then workgroups
-    const int R = p.R;
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int q = 0; q <= RR; ++q) {
-            double x = part[t][q];
-            x += __shfl_xor(x, 32);
-            if (h == 0 && q <= R) atomicAdd(&sm.red[32 * t + col][q], x);
-        }
-    __syncthreads();
-    if (v1 > v0)
         for (int e = tid; e < C * (1 + R); e += 256) {
             const int c = e / (1 + R), q = e % (1 + R);
             if (c < p.C) atomicAdd(&p.sums[(int64_t)c * (1 + R) + q], sm.red[c][q] * PSI_UNSCALE);
         }
+    }
     if constexpr (SAFE) {
         // the last workgroup clears the flag and the count for the next launch
         __shared__ bool last;
@@ -574,16 +633,20 @@ void launch_ntd(const EParams &p, hipStream_t st)
 {
     const int64_t nb = (p.n + ROWS - 1) / ROWS;
     const int64_t pairs = (nb + 1) / 2;
-    // pieces per block pair: about 64 workgroups per compute unit in all (the
-    // last partial wave of workgroups then costs a few percent), no piece
-    // shorter than two chunks
-    const int64_t chunks = (p.n + JC - 1) / JC;
+    // pieces per block pair: about 16 k in all, none shorter than two chunks
     int64_t K = (16384 + pairs - 1) / pairs;
-    K = K > chunks / 2 ? chunks / 2 : K;
+    K = K > nb / 2 ? nb / 2 : K;
     K = K < 1 ? 1 : K;
+    // chunks in all, and workgroups: two per compute unit are resident (128
+    // columns); shares of about 64 chunks keep a workgroup's set-up and
+    // reduction below a few percent, and 16 rounds of shares even out the end
+    const int64_t total = nb * (nb + 1) / 2;
+    int64_t grid = total / 64;
+    grid = grid < WG_MIN ? WG_MIN : grid > WG_MAX ? WG_MAX : grid;
+    if (grid > (total + 1) / 2) grid = (total + 1) / 2;
     // one of the two instantiations works (the range check's flag), the other exits
-    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, false>), dim3((unsigned)(pairs * K)), dim3(256), 0, st, p, (int)K);
-    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, true>), dim3((unsigned)(pairs * K)), dim3(256), 0, st, p, (int)K);
+    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, false>), dim3((unsigned)grid), dim3(256), 0, st, p, (int)K, total);
+    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, true>), dim3((unsigned)grid), dim3(256), 0, st, p, (int)K, total);
 }
 
 template <int NT, int RR>

@@ -509,3 +509,21 @@ def test_T_at_scale_against_oracle(tp):
           f"max |dT| {np.abs(np.array(T3[:len(b3)]) - want3).max():.3e}", flush=True)
     assert tol3.max() <= 0.02 * spread3
     assert np.all(np.abs(np.array(T3[:len(b3)]) - want3) <= tol3)
+
+
+@pytest.mark.parametrize("n,C,R", [(2, 32, 0), (128, 128, 1), (129, 64, 2), (385, 128, 3), (2049, 32, 1),
+                                   (12345, 128, 2), (12417, 64, 3)])
+def test_pairsums_work_split(tp, n, C, R):
+    """Sizes at the edges of the work split: one and two row blocks, an odd and an even number of them (the
+    middle block has no partner), a last block of one row, shares of the chunk sequence that begin and end inside
+    a block pair.  Against dense float64 sums on the same float32 coordinates; the library promises 1e-5."""
+    ch, s = sample(n, 300 + n)
+    Y = tp.coords(tp.DeviceSample.from_sample(s), MASKS, 1e-3)
+    rng = np.random.default_rng(n)
+    cols = (rng.uniform(size=(n, C)) < 0.5).astype(np.uint8)
+    cols[0, :] = cols[n - 1, :] = 1      # the only pair of n = 2, and the last block's row, in every column
+    sums = tp.pairsums(Y, torch.from_numpy(cols).cuda(), 0.3, nrow=R)
+    torch.cuda.synchronize()
+    M = energy.column_pair_sums(Y.cpu().numpy(), cols, 0.3)
+    want = np.stack([np.diag(M)] + [M[q] for q in range(R)], axis=1)
+    assert np.all(np.abs(sums.cpu().numpy() - want) <= 1e-5 * np.abs(want))
