@@ -69,8 +69,9 @@ constexpr int ROWS = 128;     // rows i per workgroup (4 waves x 32)
 constexpr int JC = 128;       // j per LDS chunk
 constexpr int KS = 16;        // j per matrix-core step
 constexpr int FL = 8;         // chunks per float32 -> float64 reduction
-constexpr int WG_MIN = 512;   // workgroups of a launch (see launch_ntd)
-constexpr int WG_MAX = 8192;
+constexpr int XCDS = 8;       // dies with an L2 each; workgroups go to them in turn
+constexpr int RESIDENT = 512; // workgroups that run at a time (two per compute unit at 128 columns)
+constexpr int64_t L2_BYTES = 3 << 20;   // a sample that stays in each 4 MiB L2
 constexpr int GPAD = 8;       // float16 padding per staged column (spreads LDS banks)
 constexpr int XS = 40;        // float16 slots per staged j vector: 32 used, 8 padding (spreads LDS banks)
 constexpr float PSI_LOG2 = 14.0f;             // psi is formed scaled by 2^14
@@ -83,17 +84,15 @@ constexpr double PSI_UNSCALE = 1.0 / 16384.0;
 template <int NT, bool SAFE>
 struct Smem {
     static constexpr int C = 32 * NT;
-    uint16_t xh[JC][XS];                // chunk j distance operands, float16 slots (see slot())
+    uint16_t xh[2][JC][XS];             // distance operands of this chunk and the next, float16 slots (see slot())
+    uint16_t gs[C][JC + GPAD];          // columns of the chunk, [c][j], float16 0 or 1
     float cw[4][MAXD];                  // per-wave coordinate sums for the centre c
     float cen[MAXD];                    // the centre c
-    union {
-        uint16_t gs[C][JC + GPAD];      // columns of the chunk, [c][j], float16 0 or 1
-        uint8_t gi[ROWS * C];           // row block set-up only: columns of the block's rows, [i][c]
-    };
     double red[C][1 + MAXR];            // workgroup totals
-    // SAFE: raw coordinates of the block's rows and of the chunk's events (direct distances)
-    float yr[SAFE ? ROWS : 1][MAXD + 1];
-    float yc[SAFE ? JC : 1][MAXD];
+    // SAFE: raw coordinates of the two chunks (direct distances), and whether an event of
+    // the first / second 64 of each is outside the matrix-core range
+    float yc[2][SAFE ? JC : 1][MAXD];
+    uint32_t far[2][2];
 };
 
 // The centre's scratch of the range check (same fields as Smem).
@@ -153,60 +152,83 @@ __device__ __forceinline__ void split16(const float (&x)[KA], uint16_t (&hi)[KA]
     }
 }
 
-// What a lane keeps of its wave's 32 rows for the flush: bit r of g[t] is the
-// column value G[row][32 t + col], bit r of w[q] the row weight G[row][q], row =
-// 8 (r / 4) + 4 h + r % 4 (the lane's rows in a product tile).
-template <int NT, int RR>
-struct RowBits {
+// What a lane keeps of its wave's 32 rows of a row block: its row's operand
+// halves, its row's raw coordinates (SAFE), and for the flush, bit r of g[t] the
+// column value G[row][32 t + col] and bit r of w[q] the row weight G[row][q],
+// row = 8 (r / 4) + 4 h + r % 4 (the lane's rows in a product tile).
+template <int NT, int NS, int RR, bool SAFE>
+struct Rows {
+    u32x4 xi[2];
+    float y[SAFE ? 2 * NS - 2 : 1];
     uint32_t g[NT];
     uint32_t w[RR];
+    bool far;           // SAFE: a row of the block is outside the matrix-core range
 };
 
-// Row block setup: column and weight bits of rows ib .. ib + ROWS - 1 (staged
-// through LDS once, in the space of the chunk's columns, and kept in registers),
-// and this lane's operand halves of its row's vector x_i = (-2 (y_i - c), 1,
-// |y_i - c|^2) (scaled coordinates, so psi = 2^-(scaled distance)^2):
-// x_i . x_j = |y_i - y_j|^2 for the chunk vectors x_j.  Lane half h holds
-// slots 16 m + 8 h .. + 7 of the row pattern for the two distance steps m.
-// The caller's next write of the chunk's columns follows a barrier.
+// Row block setup, each wave for itself: rows ib .. ib + 31, the wave's share of
+// the block of ROWS rows that starts at block0.  This lane's row vector is
+// x_i = (-2 (y_i - c), 1, |y_i - c|^2) (scaled coordinates, so psi =
+// 2^-(scaled distance)^2): x_i . x_j = |y_i - y_j|^2 for the chunk vectors x_j.
+// Lane half h holds slots 16 m + 8 h .. + 7 of the row pattern for the two
+// distance steps m.
 template <int NT, int NS, int RR, bool SAFE>
-__device__ __forceinline__ bool setup_rows(const EParams &p, Smem<NT, SAFE> &sm, int64_t ib, u32x4 (&xi)[2],
-                                           RowBits<NT, RR> &rb)
+__device__ __forceinline__ void setup_rows(const EParams &p, const Smem<NT, SAFE> &sm, int64_t block0, int64_t ib,
+                                           Rows<NT, NS, RR, SAFE> &rb)
 {
     constexpr int C = 32 * NT;
     constexpr int KA = 2 * NS;
-    const int tid = threadIdx.x;
-    const int h = (tid >> 5) & 1;
-    const int col = tid & 31;
-    const int64_t i = ib + (tid >> 6) * 32 + col;
-    __syncthreads();
-    for (int e = tid; e < ROWS * C / 16; e += 256) {
-        const int64_t r = ib + (e * 16) / C;
-        u32x4 w = u32x4{ 0u, 0u, 0u, 0u };
-        if (r < p.n) w = reinterpret_cast<const u32x4 *>(p.G + ib * C)[e];
-        reinterpret_cast<u32x4 *>(sm.gi)[e] = w;
+    const int lane = threadIdx.x & 63;
+    const int h = lane >> 5;
+    const int col = lane & 31;
+    const int64_t i = ib + col;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) rb.g[t] = 0u;
+#pragma unroll
+    for (int q = 0; q < RR; ++q) rb.w[q] = 0u;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int64_t row = ib + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (row < p.n) {
+            const uint8_t *G = p.G + row * C;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) rb.g[t] |= (uint32_t)G[32 * t + col] << r;
+#pragma unroll
+            for (int q = 0; q < RR; ++q) rb.w[q] |= (q < p.R ? (uint32_t)G[q] : 0u) << r;
+        }
     }
     float x[KA];
     float nrm = 0.0f;
 #pragma unroll
     for (int k = 0; k < KA; ++k) x[k] = 0.0f;
-    const int rl = (tid >> 6) * 32 + col;
 #pragma unroll
     for (int d = 0; d < KA - 2; ++d) {
         const float y = (d < p.D && i < p.n) ? p.Y[d * p.ldY + i] : 0.0f;
         const float v = (d < p.D && i < p.n) ? y * p.yscale - sm.cen[d] : 0.0f;
         nrm = fmaf(v, v, nrm);
         if (d < p.D) x[d] = -2.0f * v;
-        if constexpr (SAFE)
-            if (h == 0 && d < p.D) sm.yr[rl][d] = y;
+        if constexpr (SAFE) rb.y[d] = y;
     }
-    // outside the matrix-core range (only in the SAFE form, by the range check):
-    // finite placeholders; the chunks of this row block take the direct distances
-    const bool far = !(nrm <= VMAX2);
-    if (SAFE && far) {
-        nrm = 0.0f;
+    rb.far = false;
+    if constexpr (SAFE) {
+        // outside the matrix-core range: finite placeholders; the chunks of the
+        // whole row block take the direct distances
+        if (!(nrm <= VMAX2)) {
+            nrm = 0.0f;
 #pragma unroll
-        for (int k = 0; k < KA; ++k) x[k] = 0.0f;
+            for (int k = 0; k < KA; ++k) x[k] = 0.0f;
+        }
+        bool far = false;
+#pragma unroll
+        for (int e = 0; e < ROWS; e += 64) {
+            const int64_t j = block0 + e + lane;
+            float nj = 0.0f;
+            for (int d = 0; d < p.D; ++d) {
+                const float v = j < p.n ? p.Y[d * p.ldY + j] * p.yscale - sm.cen[d] : 0.0f;
+                nj = fmaf(v, v, nj);
+            }
+            far = far || !(nj <= VMAX2);
+        }
+        rb.far = __any(far) != 0;
     }
 #pragma unroll
     for (int k = 0; k < KA; ++k) {
@@ -220,24 +242,8 @@ __device__ __forceinline__ bool setup_rows(const EParams &p, Smem<NT, SAFE> &sm,
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const int s0 = 16 * m + 8 * h + 2 * w;
-            xi[m][w] = (uint32_t)slot<KA, false>(hi, lo, s0) | ((uint32_t)slot<KA, false>(hi, lo, s0 + 1) << 16);
+            rb.xi[m][w] = (uint32_t)slot<KA, false>(hi, lo, s0) | ((uint32_t)slot<KA, false>(hi, lo, s0 + 1) << 16);
         }
-    bool any = false;
-    if constexpr (SAFE) any = __syncthreads_or(far) != 0;
-    else __syncthreads();
-#pragma unroll
-    for (int t = 0; t < NT; ++t) rb.g[t] = 0u;
-#pragma unroll
-    for (int q = 0; q < RR; ++q) rb.w[q] = 0u;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const uint8_t *row = sm.gi + ((tid >> 6) * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * C;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) rb.g[t] |= (uint32_t)row[32 * t + col] << r;
-#pragma unroll
-        for (int q = 0; q < RR; ++q) rb.w[q] |= (q < p.R ? (uint32_t)row[q] : 0u) << r;
-    }
-    return any;
 }
 
 // Position of local j in a staged column: bits 2 and 3 swapped, the order in
@@ -245,178 +251,322 @@ __device__ __forceinline__ bool setup_rows(const EParams &p, Smem<NT, SAFE> &sm,
 // chunk_products).
 __device__ __forceinline__ int swap23(int j) { return (j & ~12) | ((j & 4) << 1) | ((j & 8) >> 1); }
 
-// Stage chunk j0 .. j0 + JC - 1: the vectors x_j = (y_j - c, |y_j - c|^2, 1)
-// as [k][j] (padding events j >= n get y_j = c, so every psi stays finite; their
-// columns are 0), and the columns transposed to [c][swap23(j)] as float16.
-// Each item takes 4 rows x 16 columns (four 16-byte loads) and writes, per
-// column, the 4 rows as one 8-byte word: bytes b of two rows are placed as the
-// 16-bit lanes of one word (b0 | b1 << 16), and the 24-bit multiply by 0x3C00
-// turns each lane's 0/1 into float16 0 or 1.0.
-// One chunk in flight in registers: thread tid < JC holds the coordinates of
-// event j0 + tid, thread it < ITEMS the 4 rows x 16 columns of its item.  The
-// loads for chunk v + 1 are issued before chunk v is multiplied and written to
-// LDS after it, so their latency hides behind the products.
-template <int KA>
-struct Pending {
-    float y[KA - 2];
-    u32x4 w[4];
+// Load element i (32-bit index) from a uniform base pointer: the byte offset is
+// formed in 32 bits, so the load takes the scalar-base + vector-offset form.
+template <typename T>
+__device__ __forceinline__ T ld(const void *base, uint32_t byte)
+{
+    typedef const T __attribute__((address_space(1))) *gptr;
+    return *(gptr)((const char *)base + byte);
+}
+
+template <int N> struct Words;
+template <> struct Words<1> { typedef uint32_t t; };
+template <> struct Words<2> { typedef u32x2 t; };
+template <> struct Words<4> { typedef u32x4 t; };
+
+// Staging.  Columns of chunk j0 .. j0 + JC - 1 go to LDS transposed, [c][swap23(j)],
+// as float16 (events j >= n: 0).  A thread takes 4 rows x 4 NT columns, one load of
+// 4 NT bytes per row, and writes, per column, its 4 rows as one 8-byte word.  A dword
+// of four 0/1 bytes times 60, in two 16-bit lanes, holds 0x3C for each 1, the high byte
+// of float16 1.0; a byte permute then places the column's bytes of two rows in the high
+// bytes of the two halves of a word.
+// A chunk wholly inside the sample (``full``, uniform) takes unconditional loads off
+// scalar bases, which cost no vector instructions.
+template <int NT>
+struct Columns {
+    typename Words<NT>::t w[4];
 };
 
-template <int NT, int KA>
-__device__ __forceinline__ void load_chunk(const EParams &p, int64_t j0, Pending<KA> &pd)
+template <int NT>
+__device__ __forceinline__ void load_columns(const EParams &p, int64_t j0, Columns<NT> &pd)
 {
+    typedef typename Words<NT>::t W;
     constexpr int C = 32 * NT;
-    constexpr int ITEMS = (JC / 4) * (C / 16);
-    static_assert(ITEMS <= 256, "one item per thread");
     const int tid = threadIdx.x;
-    const int64_t j = j0 + tid;
+    const uint32_t item = (uint32_t)((tid & 31) * 4 * C + (tid >> 5) * 4 * NT);
+    const uint8_t *G = p.G + j0 * C;
+    if (j0 + JC <= p.n) {
 #pragma unroll
-    for (int d = 0; d < KA - 2; ++d) pd.y[d] = (tid < JC && d < p.D && j < p.n) ? p.Y[d * p.ldY + j] : 0.0f;
-    const int jq = (tid % (JC / 4)) * 4;
-    const int cg = tid / (JC / 4);
+        for (int rr = 0; rr < 4; ++rr) pd.w[rr] = ld<W>(G, item + rr * C);
+    } else {
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+            W z;
+            __builtin_memset(&z, 0, sizeof z);
+            pd.w[rr] = j0 + (tid & 31) * 4 + rr < p.n ? ld<W>(G, item + rr * C) : z;
+        }
+    }
+}
+
+template <int NT>
+__device__ __forceinline__ void expand_columns(const Columns<NT> &pd, u32x2 (&o)[4 * NT])
+{
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    uint32_t w[4][NT];
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
-        const int64_t jr = j0 + jq + rr;
-        pd.w[rr] = (tid < ITEMS && jr < p.n) ? *reinterpret_cast<const u32x4 *>(p.G + jr * C + 16 * cg) : u32x4{ 0u, 0u, 0u, 0u };
+        __builtin_memcpy(w[rr], &pd.w[rr], sizeof w[rr]);
+#pragma unroll
+        for (int e = 0; e < NT; ++e)
+            w[rr][e] = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, w[rr][e]) * (uint16_t)60));
+    }
+#pragma unroll
+    for (int q = 0; q < 4 * NT; ++q) {
+        const int m = q & 3, e = q >> 2;
+        // zero, byte m of the second source (first row of the pair), zero, byte m of the first source
+        const uint32_t sel = 0x0cu | ((uint32_t)m << 8) | (0x0cu << 16) | ((uint32_t)(4 + m) << 24);
+        o[q] = u32x2{ __builtin_amdgcn_perm(w[1][e], w[0][e], sel), __builtin_amdgcn_perm(w[3][e], w[2][e], sel) };
+    }
+}
+
+template <int NT, bool SAFE>
+__device__ __forceinline__ void store_columns(Smem<NT, SAFE> &sm, const u32x2 (&o)[4 * NT])
+{
+    const int tid = threadIdx.x;
+    const int jq = swap23((tid & 31) * 4);
+    const int c0 = (tid >> 5) * 4 * NT;
+#pragma unroll
+    for (int q = 0; q < 4 * NT; ++q) *reinterpret_cast<u32x2 *>(&sm.gs[c0 + q][jq]) = o[q];
+}
+
+// The vectors x_j = (y_j - c, |y_j - c|^2, 1) go to LDS as [j][slot], one event per
+// thread of the first two waves (padding events j >= n get y_j = c, so every psi stays
+// finite).  The groups of 8 slots past the last term are the same for every event.
+template <int KA>
+struct Event {
+    float y[KA - 2];
+};
+
+template <int KA>
+__device__ __forceinline__ void load_events(const EParams &p, int64_t j0, Event<KA> &pd)
+{
+    const int tid = threadIdx.x;
+    if (tid >= JC) return;
+    if (j0 + JC <= p.n) {
+#pragma unroll
+        for (int d = 0; d < KA - 2; ++d)
+            pd.y[d] = d < KA - 3 || d < p.D ? ld<float>(p.Y + d * p.ldY + j0, 4u * tid) : 0.0f;
+    } else {
+#pragma unroll
+        for (int d = 0; d < KA - 2; ++d) pd.y[d] = (d < p.D && j0 + tid < p.n) ? p.Y[d * p.ldY + j0 + tid] : 0.0f;
+    }
+}
+
+template <int KA>
+constexpr int slot_groups() { return (3 * KA + 7) / 8; }
+
+template <int NT, int KA, bool SAFE>
+__device__ __forceinline__ void fill_slots(Smem<NT, SAFE> &sm)
+{
+    const uint16_t none[KA] = {};
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int q = slot_groups<KA>(); q < 4; ++q) {
+        u32x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            w[e] = (uint32_t)slot<KA, true>(none, none, 8 * q + 2 * e) |
+                   ((uint32_t)slot<KA, true>(none, none, 8 * q + 2 * e + 1) << 16);
+        *reinterpret_cast<u32x4 *>(&sm.xh[tid / JC][tid % JC][8 * q]) = w;
     }
 }
 
 template <int NT, int KA, bool SAFE>
-__device__ __forceinline__ bool store_chunk(const EParams &p, Smem<NT, SAFE> &sm, int64_t j0, const Pending<KA> &pd)
+__device__ __forceinline__ void store_events(const EParams &p, Smem<NT, SAFE> &sm, int b, int64_t j0, const Event<KA> &pd)
 {
-    constexpr int C = 32 * NT;
-    constexpr int ITEMS = (JC / 4) * (C / 16);
     const int tid = threadIdx.x;
-    bool far = false;
-    if (tid < JC) {
-        const bool real = j0 + tid < p.n;   // padding events sit at the centre
-        float x[KA];
-        float nrm = 0.0f;
+    if (tid >= JC) return;
+    const bool real = j0 + JC <= p.n || j0 + tid < p.n;
+    const bool all = p.D == KA - 2;             // else D = KA - 3
+    float x[KA];
+    float nrm = 0.0f;
 #pragma unroll
-        for (int k = 0; k < KA; ++k) x[k] = 0.0f;
-#pragma unroll
-        for (int d = 0; d < KA - 2; ++d) {
-            const float v = (d < p.D && real) ? pd.y[d] * p.yscale - sm.cen[d] : 0.0f;
-            nrm = fmaf(v, v, nrm);
-            if (d < p.D) x[d] = v;
-            if constexpr (SAFE)
-                if (d < p.D) sm.yc[tid][d] = real ? pd.y[d] : 0.0f;
-        }
-        far = !(nrm <= VMAX2);
-        if (SAFE && far) {
+    for (int d = 0; d < KA - 2; ++d) {
+        const float v = (d < KA - 3 || all) && real ? pd.y[d] * p.yscale - sm.cen[d] : 0.0f;
+        nrm = fmaf(v, v, nrm);
+        x[d] = v;
+        if constexpr (SAFE) sm.yc[b][tid][d] = real ? pd.y[d] : 0.0f;
+    }
+    if constexpr (SAFE) {
+        const bool far = !(nrm <= VMAX2);
+        const bool any = __any(far) != 0;
+        if ((tid & 63) == 0) sm.far[b][tid >> 6] = any;
+        if (far) {
             nrm = 0.0f;
 #pragma unroll
-            for (int k = 0; k < KA; ++k) x[k] = 0.0f;
-        }
-#pragma unroll
-        for (int k = 0; k < KA; ++k) {
-            if (k == p.D) x[k] = nrm;
-            if (k == p.D + 1) x[k] = 1.0f;
-        }
-        uint16_t hi[KA], lo[KA];
-        split16<KA>(x, hi, lo);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            u32x4 w;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int s0 = 8 * q + 2 * e;
-                w[e] = (uint32_t)slot<KA, true>(hi, lo, s0) | ((uint32_t)slot<KA, true>(hi, lo, s0 + 1) << 16);
-            }
-            *reinterpret_cast<u32x4 *>(&sm.xh[tid][8 * q]) = w;
+            for (int k = 0; k < KA - 2; ++k) x[k] = 0.0f;
         }
     }
-    if (tid < ITEMS) {
-        const int jq = (tid % (JC / 4)) * 4;
-        const int cg = tid / (JC / 4);
+    x[KA - 3] = all ? x[KA - 3] : nrm;
+    x[KA - 2] = all ? nrm : 1.0f;
+    x[KA - 1] = all ? 1.0f : 0.0f;
+    uint16_t hi[KA], lo[KA];
+    split16<KA>(x, hi, lo);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int m = q & 3, wd = q >> 2;
-            // byte m of the second source (first row of the pair) to bits 0..7,
-            // byte m of the first source (second row) to bits 16..23, zeros elsewhere
-            const uint32_t sel = (uint32_t)m | (0x0cu << 8) | ((uint32_t)(4 + m) << 16) | (0x0cu << 24);
-            const uint32_t x01 = __builtin_amdgcn_perm(pd.w[1][wd], pd.w[0][wd], sel);
-            const uint32_t x23 = __builtin_amdgcn_perm(pd.w[3][wd], pd.w[2][wd], sel);
-            *reinterpret_cast<u32x2 *>(&sm.gs[16 * cg + q][swap23(jq)]) = u32x2{ (uint32_t)__umul24(x01, 0x3C00u), (uint32_t)__umul24(x23, 0x3C00u) };
+    for (int q = 0; q < slot_groups<KA>(); ++q) {
+        u32x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int s0 = 8 * q + 2 * e;
+            w[e] = (uint32_t)slot<KA, true>(hi, lo, s0) | ((uint32_t)slot<KA, true>(hi, lo, s0 + 1) << 16);
         }
+        *reinterpret_cast<u32x4 *>(&sm.xh[b][tid][8 * q]) = w;
     }
-    return far;
 }
 
-// psi products of one staged chunk into the float32 tiles, 32 j per step.
-// The distances come from the matrix cores too: the 32 float16 slots of the
-// column and row vectors (two v_mfma_f32_32x32x16_f16) give lane (col, h)
-// |y_i - y_j|^2 - 14 for its row i and the 16 j = 8 (r / 4) + 4 h + r % 4,
-// r < 16.  Then psi * 2^14 = 2^-(that), split into float16 hi and lo.
-// Taken in pairs of r, the values for r < 8 are the lane's 8 consecutive k of
-// the first 32 x 16 psi tile and r >= 8 those of the second; k = 8 h + (r % 8)
-// stands for local j = 8 (r % 8 / 4) + 4 h + r % 4 (+16 for the second tile),
-// which is k with bits 2 and 3 swapped, the order in which the columns are
-// staged.  MASK keeps only j > rel (rel = i - j0), needed only in the chunk
-// that holds the diagonal.
-// DIRECT (SAFE form only): the distances of the chunk as direct float32
-// differences of the raw coordinates instead, |(y_i - y_j) yscale|^2 - 14 for
-// the same lane layout.
-template <int NT, bool MASK, bool SAFE, bool DIRECT>
-__device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, const u32x4 (&xi)[2], int rel,
-                                               f32x16 (&acc)[NT], int D, float yscale)
+// Squared distances (minus 14) of local j = jb .. jb + 31 against the wave's 32
+// rows, 32 float16 slots of the column and row vectors (two
+// v_mfma_f32_32x32x16_f16): lane (col, h) gets row col and the 16 j =
+// jb + 8 (r / 4) + 4 h + r % 4, r < 16.  DIRECT (SAFE form only): as direct
+// float32 differences of the raw coordinates instead, |(y_i - y_j) yscale|^2 - 14,
+// in the same lane layout.
+template <int NT, int NS, int RR, bool SAFE, bool DIRECT>
+__device__ __forceinline__ f32x16 distances(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, RR, SAFE> &rb, int jb, int D,
+                                            float yscale)
+{
+    const int lane = threadIdx.x & 63;
+    const int h = lane >> 5;
+    const int col = lane & 31;
+    f32x16 dd = f32x16{};
+    if constexpr (DIRECT) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int j = jb + 8 * (r >> 2) + 4 * h + (r & 3);
+            float d2 = 0.0f;
+#pragma unroll
+            for (int d = 0; d < 2 * NS - 2; ++d) {
+                if (d < 2 * NS - 3 || d < D) {
+                    const float t = (rb.y[d] - sm.yc[b][j][d]) * yscale;
+                    d2 = fmaf(t, t, d2);
+                }
+            }
+            dd[r] = d2 - PSI_LOG2;
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const f16x8 A = *reinterpret_cast<const f16x8 *>(&sm.xh[b][jb + col][16 * m + 8 * h]);
+            dd = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, __builtin_bit_cast(f16x8, rb.xi[m]), dd, 0, 0, 0);
+        }
+    }
+    return dd;
+}
+
+// psi * 2^14 = 2^-dd of one step, split into float16 hi and lo: the operand
+// tiles of the contraction.  Taken in pairs k of r = 2 k, 2 k + 1, the values
+// for r < 8 are the lane's 8 consecutive k of the first 32 x 16 psi tile and
+// r >= 8 those of the second; k = 8 h + (r % 8) stands for local
+// j = 8 (r % 8 / 4) + 4 h + r % 4 (+16 for the second tile), which is k with
+// bits 2 and 3 swapped, the order in which the columns are staged.
+struct Psi {
+    u32x4 hi[2], lo[2];
+};
+
+// Pair k of a step at local j = jb.  MASK keeps only j > rel (rel = i - j0),
+// needed only in the chunk that holds the diagonal.
+template <bool MASK>
+__device__ __forceinline__ void psi_pair(const f32x16 &dd, int k, int jb, int rel, Psi &o)
+{
+    const int h = (threadIdx.x >> 5) & 1;
+    const int r = 2 * k;
+    float a = __builtin_amdgcn_exp2f(-dd[r]);
+    float b = __builtin_amdgcn_exp2f(-dd[r + 1]);
+    if (MASK) {
+        const int ja = jb + 8 * (r >> 2) + 4 * h + (r & 3);
+        a = (ja > rel) ? a : 0.0f;
+        b = (ja + 1 > rel) ? b : 0.0f;
+    }
+    const uint32_t hw = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+    // residuals a - hi_a, b - hi_b, each one mixed-precision multiply-add
+    // reading its float16 half of hw directly (exact: hi is a truncation of a)
+    float ra, rb;
+    asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(ra) : "v"(hw), "v"(a));
+    asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rb) : "v"(hw), "v"(b));
+    o.hi[k >> 2][k & 3] = hw;
+    o.lo[k >> 2][k & 3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(ra, rb));
+}
+
+// psi of a chunk's first step.
+template <int NT, int NS, int RR, bool SAFE, bool DIRECT>
+__device__ __forceinline__ void first_psi(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, RR, SAFE> &rb, Psi &cur, int D,
+                                          float yscale)
+{
+    const f32x16 dd = distances<NT, NS, RR, SAFE, DIRECT>(sm, b, rb, 0, D, yscale);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) psi_pair<false>(dd, k, 0, 0, cur);
+}
+
+// psi products of one staged chunk into the float32 tiles, 32 j per step, the
+// steps pipelined in each wave: while the matrix cores contract step s (4 NT
+// MFMAs), the vector ALU forms psi of step s + 1 from the distances issued just
+// ahead.  An MFMA holds the matrix core for 32 cycles and the wave's issue for
+// 4, so the psi instructions (16 exp2 and 32 conversions and residuals, about
+// 270 cycles a step) fit between the MFMAs (512 cycles a step at 128 columns);
+// the fences keep the interleaving, which the scheduler would undo.  The
+// pipeline runs on into the next chunk: ``cur`` enters holding psi of this
+// chunk's first step and leaves with that of the next one's, which is of use
+// when that is the row block's next chunk (SAFE: each chunk for itself).
+template <int NT, int NS, int RR, bool SAFE, bool DIRECT>
+__device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, int b,
+                                               const Rows<NT, NS, RR, SAFE> &rb, f32x16 (&acc)[NT], Psi &cur, int D,
+                                               float yscale)
+{
+    const int lane = threadIdx.x & 63;
+    const int h = lane >> 5;
+    const int col = lane & 31;
+    constexpr int Q = 2 * NT;             // (psi tile, column tile) items per step
+    constexpr int STEPS = JC / (2 * KS);
+    // operand of item e (counted over the chunk's steps), read one item ahead of its use
+    auto column = [&](int e) {
+        const int jb = e / Q * 2 * KS, q = e % Q;
+        return *reinterpret_cast<const f16x8 *>(&sm.gs[32 * (q % NT) + col][jb + KS * (q / NT) + 8 * h]);
+    };
+    f16x8 B0 = column(0);
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const bool last = st + 1 == STEPS;
+        f32x16 dd = f32x16{};
+        if (!last) dd = distances<NT, NS, RR, SAFE, DIRECT>(sm, b, rb, (st + 1) * 2 * KS, D, yscale);
+        else if (!SAFE) dd = distances<NT, NS, RR, SAFE, false>(sm, b ^ 1, rb, 0, D, yscale);
+        Psi next;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int e = st * Q + q, m = q / NT, t = q % NT;
+            const f16x8 B = B0;
+            if (e + 1 < STEPS * Q) B0 = column(e + 1);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, cur.hi[m]), B, acc[t], 0, 0, 0);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, cur.lo[m]), B, acc[t], 0, 0, 0);
+#pragma unroll
+            for (int k = 8 * q / Q; k < 8 * (q + 1) / Q; ++k)
+                if (!last || !SAFE) psi_pair<false>(dd, k, 0, 0, next);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!last || !SAFE) cur = next;
+    }
+}
+
+// The chunk that holds the diagonal of the wave's rows, which is its row
+// block's first: step by step, keeping psi only for j > rel.
+template <int NT, int NS, int RR, bool SAFE, bool DIRECT>
+__device__ __forceinline__ void diagonal_products(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, RR, SAFE> &rb, int rel,
+                                                  f32x16 (&acc)[NT], int D, float yscale)
 {
     const int lane = threadIdx.x & 63;
     const int h = lane >> 5;
     const int col = lane & 31;
 #pragma unroll 1
     for (int jb = 0; jb < JC; jb += 2 * KS) {
-        f32x16 dd = f32x16{};
-        if constexpr (DIRECT) {
-            const int row = (threadIdx.x >> 6) * 32 + col;
+        const f32x16 dd = distances<NT, NS, RR, SAFE, DIRECT>(sm, b, rb, jb, D, yscale);
+        Psi psi;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int j = jb + 8 * (r >> 2) + 4 * h + (r & 3);
-                float d2 = 0.0f;
-                for (int d = 0; d < D; ++d) {
-                    const float t = (sm.yr[row][d] - sm.yc[j][d]) * yscale;
-                    d2 = fmaf(t, t, d2);
-                }
-                dd[r] = d2 - PSI_LOG2;
-            }
-        } else {
+        for (int k = 0; k < 8; ++k) psi_pair<true>(dd, k, jb, rel, psi);
 #pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const f16x8 A = *reinterpret_cast<const f16x8 *>(&sm.xh[jb + col][16 * m + 8 * h]);
-                dd = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, __builtin_bit_cast(f16x8, xi[m]), dd, 0, 0, 0);
-            }
-        }
-        u32x4 ah[2], al[2];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int r = 2 * k;
-            float a = __builtin_amdgcn_exp2f(-dd[r]);
-            float b = __builtin_amdgcn_exp2f(-dd[r + 1]);
-            if (MASK) {
-                const int ja = jb + 8 * (r >> 2) + 4 * h + (r & 3);
-                a = (ja > rel) ? a : 0.0f;
-                b = (ja + 1 > rel) ? b : 0.0f;
-            }
-            const uint32_t hw = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
-            // residuals a - hi_a, b - hi_b, each one mixed-precision multiply-add
-            // reading its float16 half of hw directly (exact: hi is a truncation of a)
-            float ra, rb;
-            asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(ra) : "v"(hw), "v"(a));
-            asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rb) : "v"(hw), "v"(b));
-            ah[k >> 2][k & 3] = hw;
-            al[k >> 2][k & 3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(ra, rb));
-        }
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            const f16x8 A_hi = __builtin_bit_cast(f16x8, ah[m]);
-            const f16x8 A_lo = __builtin_bit_cast(f16x8, al[m]);
-            const int jl = jb + KS * m + 8 * h;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const f16x8 B = *reinterpret_cast<const f16x8 *>(&sm.gs[32 * t + col][jl]);
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A_hi, B, acc[t], 0, 0, 0);
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A_lo, B, acc[t], 0, 0, 0);
-            }
+        for (int q = 0; q < 2 * NT; ++q) {
+            const int m = q / NT, t = q % NT;
+            const f16x8 B = *reinterpret_cast<const f16x8 *>(&sm.gs[32 * t + col][jb + KS * m + 8 * h]);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, psi.hi[m]), B, acc[t], 0, 0, 0);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, psi.lo[m]), B, acc[t], 0, 0, 0);
         }
     }
 }
@@ -426,8 +576,8 @@ __device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, const u
 // wave's 32.  The leading R columns are the row weights; their values
 // (Psi_upper w_q)_i come from the lane that holds them (lane q of the half), so
 // that every column can take the transposed term sum_i G_ic (Psi_upper w_q)_i.
-template <int NT, int RR>
-__device__ __forceinline__ void flush(const RowBits<NT, RR> &rb, f32x16 (&acc)[NT], double (&part)[NT][1 + RR])
+template <int NT, int NS, int RR, bool SAFE>
+__device__ __forceinline__ void flush(const Rows<NT, NS, RR, SAFE> &rb, f32x16 (&acc)[NT], double (&part)[NT][1 + RR])
 {
     const int src = threadIdx.x & 32;
     float s0[NT], s1[NT], s2[NT], s3[NT];
@@ -465,15 +615,13 @@ __device__ __forceinline__ void flush(const RowBits<NT, RR> &rb, f32x16 (&acc)[N
 // their chunks, block g's first, form one list, and the lists of all pairs in
 // turn one sequence of chunks.  Float32 accumulation runs over segments of
 // this sequence: a pair's list is cut into K equal pieces, a piece at the row
-// block's end, and the rest every FL chunks.  Workgroups take equal contiguous
-// shares of the sequence, rounded to segments, so a share costs one set-up and
+// block's end, and the rest every FL chunks.  A workgroup takes a contiguous
+// share of the sequence, rounded to segments, so a share costs one set-up and
 // one reduction however small the pieces are, and the float32 sums do not
-// depend on how many workgroups there are.  (One workgroup per piece instead:
-// at 3e4 events pieces of two chunks, 13.8 k workgroups, each with its centre,
-// its rows' columns, and 256 float64 atomics on the same addresses as the
-// others': 0.533 ms against 0.353 ms, 128 columns; at 1e5 events with two row
-// weights 3.19 against 2.69 ms; at 1e6 events 264 against 253 ms, the last from
-// the flush reading its row columns from registers instead of LDS.)
+// depend on how many workgroups there are or which share each takes.  (One
+// workgroup per piece instead: at 3e4 events pieces of two chunks, 13.8 k
+// workgroups, each with its centre, its rows' columns, and 256 float64 atomics
+// on the same addresses as the others': 0.533 ms against 0.353 ms, 128 columns.)
 struct Seq {
     int64_t n, nb;
     int K;
@@ -505,11 +653,24 @@ struct Seq {
 };
 
 // RR: row-weight columns the reduction carries (RR covers R <= RR).
+//
+// What bounds it: the 18 MFMAs per 32 x 32 pairs (128 columns, 576 cycles), and
+// the power they draw: products alone, on data that stays in LDS, run at 1.8 GHz
+// with the matrix cores 86 % busy.  The vector ALU's psi work, staging and
+// flush (about 350 instructions per wave and chunk beside 72 MFMAs) share the
+// issue, so the loop over the chunks of a segment holds nothing else: the
+// diagonal, the row set-up and the flush stand outside it, which also keeps the
+// accumulators in place and everything in registers (with the diagonal's mask
+// as a variant inside it the loop carried 70 moves and scratch reloads, and
+// the reloads waited for the loads of the next chunk).  At 3e5 events x 128
+// columns: 23.6 ms with the products unpipelined, 20.2 ms with them pipelined
+// inside a chunk, 18.8 ms in this form.
 template <int NT, int NS, int RR, bool SAFE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void tp_pairsum_kernel(const EParams p, const int K,
-                                                                                                 const int64_t total)
+                                                                                                 const int S, const int64_t total)
 {
     constexpr int C = 32 * NT;
+    constexpr int KA = 2 * NS;
     // the range check's flag selects the one instantiation that works
     const bool flagged = __atomic_load_n(p.flag, __ATOMIC_RELAXED) != 0u;
     if (flagged != SAFE) return;
@@ -520,10 +681,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
     const int h = lane >> 5;
     const int col = lane & 31;
     const Seq sq = { p.n, (p.n + ROWS - 1) / ROWS, K };
-    // this workgroup's share [pos, end) of the sequence of chunks
-    const int64_t share = total / gridDim.x, extra = total % gridDim.x, wg = blockIdx.x;
-    int64_t pos = sq.round(wg * share + (wg < extra ? wg : extra), total);
-    const int64_t end = sq.round((wg + 1) * share + (wg + 1 < extra ? wg + 1 : extra), total);
+    // this workgroup's share [pos, end) of the sequence of chunks: with S > 0 one
+    // of S parts of a pair's list (part r of every pair before part r + 1 of any,
+    // and each die given a run of this order, so that the workgroups of a die
+    // read the same chunks at about the same time), else an equal part of it all
+    int64_t pos, end;
+    if (S > 0) {
+        const uint32_t pairs = (uint32_t)((sq.nb + 1) / 2), units = gridDim.x;
+        const uint32_t xcd = blockIdx.x % XCDS, slot = blockIdx.x / XCDS;
+        const uint32_t u = xcd * (units / XCDS) + (xcd < units % XCDS ? xcd : units % XCDS) + slot;
+        const int64_t g = u % pairs, r = u / pairs, L = sq.len(g), at = g * (sq.nb + 1);
+        pos = sq.round(at + r * L / S, total);
+        end = r + 1 < S ? sq.round(at + (r + 1) * L / S, total) : at + L;
+    } else {
+        const int64_t share = total / gridDim.x, extra = total % gridDim.x, wg = blockIdx.x;
+        pos = sq.round(wg * share + (wg < extra ? wg : extra), total);
+        end = sq.round((wg + 1) * share + (wg + 1 < extra ? wg + 1 : extra), total);
+    }
     const bool works = pos < end;
     if (works) {
         for (int e = tid; e < C * (1 + MAXR); e += 256) (&sm.red[0][0])[e] = 0.0;
@@ -536,47 +710,83 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = f32x16{};
         centre(p, sm);
-        u32x4 xi[2];
-        RowBits<NT, RR> rb;
-        int64_t g = pos / (sq.nb + 1), v = pos % (sq.nb + 1), cur = -1;
+        fill_slots<NT, KA, SAFE>(sm);
+        // cursors of the sequence: this chunk, the next, the one after
+        struct Cursor { int64_t g, v; };
+        auto after = [&](Cursor c) { return c.v + 1 < sq.len(c.g) ? Cursor{ c.g, c.v + 1 } : Cursor{ c.g + 1, 0 }; };
         // ROWS == JC: a row block starts a chunk, and its first chunk holds the diagonal
-        auto chunk_j0 = [&](int64_t gg, int64_t vv) {
-            const int64_t L1 = sq.len1(gg);
-            return (vv < L1 ? gg + vv : sq.nb - 1 - gg + (vv - L1)) * JC;
+        auto chunk_j0 = [&](Cursor c) {
+            const int64_t L1 = sq.len1(c.g);
+            return (c.v < L1 ? c.g + c.v : sq.nb - 1 - c.g + (c.v - L1)) * JC;
         };
-        Pending<2 * NS> pd;
-        load_chunk<NT, 2 * NS>(p, chunk_j0(g, v), pd);
-        bool rows_far = false;
+        Cursor at = { pos / (sq.nb + 1), pos % (sq.nb + 1) }, at1 = after(at);
+        Columns<NT> cols;
+        Event<KA> ev;
+        {
+            const int64_t j0 = chunk_j0(at);
+            load_columns<NT>(p, j0, cols);
+            load_events<KA>(p, j0, ev);
+            store_events<NT, KA, SAFE>(p, sm, 0, j0, ev);
+            if (pos + 1 < end) load_events<KA>(p, chunk_j0(at1), ev);
+        }
+        __syncthreads();
+        Rows<NT, NS, RR, SAFE> rb;
+        Psi cur;
+        bool primed = false;
+        int64_t blk = -1;
+        int b = 0;
+        const int rel = wave * 32 + col;
+        // this chunk's columns and the next one's vectors to LDS, the loads after them issued
+        auto stage = [&]() {
+            u32x2 o[4 * NT];
+            expand_columns<NT>(cols, o);
+            __syncthreads();                    // the last chunk's columns have been read
+            store_columns<NT, SAFE>(sm, o);
+            if (pos + 1 < end) store_events<NT, KA, SAFE>(p, sm, b ^ 1, chunk_j0(at1), ev);
+            __syncthreads();
+            const Cursor at2 = after(at1);
+            if (pos + 1 < end) load_columns<NT>(p, chunk_j0(at1), cols);
+            if (pos + 2 < end) load_events<KA>(p, chunk_j0(at2), ev);
+            at = at1;
+            at1 = at2;
+            ++pos;
+        };
         while (pos < end) {
-            const int64_t L1 = sq.len1(g), L = sq.len(g);
-            const int64_t blk = v < L1 ? g : sq.nb - 1 - g;
+            const int64_t L1 = sq.len1(at.g), L = sq.len(at.g);
+            const int64_t row = at.v < L1 ? at.g : sq.nb - 1 - at.g;
             int64_t s0, s1;
-            sq.segment(g, v, s0, s1);
-            if (blk != cur) {
-                rows_far = setup_rows<NT, NS, RR, SAFE>(p, sm, blk * ROWS, xi, rb);
-                cur = blk;
+            sq.segment(at.g, at.v, s0, s1);
+            const bool diag = at.v == 0 || at.v == L1, more = s1 != L1 && s1 != L && pos + (s1 - s0) < end;
+            int left = (int)(s1 - s0);
+            if (row != blk) {
+                setup_rows<NT, NS, RR, SAFE>(p, sm, row * ROWS, row * ROWS + wave * 32, rb);
+                blk = row;
+                primed = false;
             }
-            for (; v < s1; ++v, ++pos) {
-                const int64_t c0 = v < L1 ? v : v - L1;      // chunk within the block's row
-                __syncthreads();
-                const bool cfar = store_chunk<NT, 2 * NS, SAFE>(p, sm, chunk_j0(g, v), pd);
-                bool far = false;
-                if constexpr (SAFE) far = __syncthreads_or(cfar) != 0 || rows_far;
-                else __syncthreads();
-                if (pos + 1 < end) load_chunk<NT, 2 * NS>(p, v + 1 < L ? chunk_j0(g, v + 1) : chunk_j0(g + 1, 0), pd);
-                if (SAFE && far) {    // uniform over the workgroup
-                    if (c0 == 0) chunk_products<NT, true, SAFE, SAFE>(sm, xi, wave * 32 + col, acc, p.D, p.yscale);
-                    else chunk_products<NT, false, SAFE, SAFE>(sm, xi, 0, acc, p.D, p.yscale);
-                } else {
-                    if (c0 == 0) chunk_products<NT, true, SAFE, false>(sm, xi, wave * 32 + col, acc, p.D, p.yscale);
-                    else chunk_products<NT, false, SAFE, false>(sm, xi, 0, acc, p.D, p.yscale);
-                }
+            if (diag) {
+                stage();
+                if (SAFE && (rb.far || (sm.far[b][0] | sm.far[b][1]) != 0u))
+                    diagonal_products<NT, NS, RR, SAFE, SAFE>(sm, b, rb, rel, acc, p.D, p.yscale);
+                else diagonal_products<NT, NS, RR, SAFE, false>(sm, b, rb, rel, acc, p.D, p.yscale);
+                b ^= 1;
+                --left;
             }
-            flush<NT, RR>(rb, acc, part);
-            if (v == L) {
-                v = 0;
-                ++g;
+            if (left > 0) {
+                if (!SAFE && !primed) first_psi<NT, NS, RR, SAFE, false>(sm, b, rb, cur, p.D, p.yscale);
+                do {
+                    stage();
+                    if (SAFE && (rb.far || (sm.far[b][0] | sm.far[b][1]) != 0u)) {
+                        first_psi<NT, NS, RR, SAFE, SAFE>(sm, b, rb, cur, p.D, p.yscale);
+                        chunk_products<NT, NS, RR, SAFE, SAFE>(sm, b, rb, acc, cur, p.D, p.yscale);
+                    } else {
+                        if (SAFE) first_psi<NT, NS, RR, SAFE, false>(sm, b, rb, cur, p.D, p.yscale);
+                        chunk_products<NT, NS, RR, SAFE, false>(sm, b, rb, acc, cur, p.D, p.yscale);
+                    }
+                    b ^= 1;
+                } while (--left > 0);
+                primed = more;
             }
+            flush<NT, NS, RR, SAFE>(rb, acc, part);
         }
         // combine the two row halves of each column, then the four waves, then workgroups
         const int R = p.R;
@@ -637,16 +847,34 @@ void launch_ntd(const EParams &p, hipStream_t st)
     int64_t K = (16384 + pairs - 1) / pairs;
     K = K > nb / 2 ? nb / 2 : K;
     K = K < 1 ? 1 : K;
-    // chunks in all, and workgroups: two per compute unit are resident (128
-    // columns); shares of about 64 chunks keep a workgroup's set-up and
-    // reduction below a few percent, and 16 rounds of shares even out the end
+    // Shares of at least about 64 chunks keep a workgroup's set-up and reduction
+    // below a few percent.  A sample that does not fit an L2 is split by pairs
+    // and parts (S), the number of parts chosen for full rounds of resident
+    // workgroups: at 3e5 events the L2 misses fall from 72 to 2 % of the
+    // requests, the time from 19.9 to 19.5 ms.  A smaller one (or one with too
+    // few pairs for that) is split evenly, in up to 16 full rounds.
     const int64_t total = nb * (nb + 1) / 2;
-    int64_t grid = total / 64;
-    grid = grid < WG_MIN ? WG_MIN : grid > WG_MAX ? WG_MAX : grid;
-    if (grid > (total + 1) / 2) grid = (total + 1) / 2;
+    int64_t S = 0, grid = total / 64;
+    if (p.n * (p.C + 4 * p.D) > L2_BYTES && pairs * 2 > RESIDENT) {
+        double best = 0.0;      // full rounds, times the share of a part that is not its set-up
+        for (int64_t s = 1; s <= 64; ++s) {
+            const int64_t u = pairs * s, len = (nb + 1) / s;
+            if (s > 1 && (len < 48 || u > 32 * RESIDENT)) break;
+            const double rounds = (double)u / RESIDENT, full = (double)((u + RESIDENT - 1) / RESIDENT);
+            const double score = rounds / full * (double)len / (double)(len + 2);
+            if (score > best) {
+                best = score;
+                S = s;
+            }
+        }
+        grid = pairs * S;
+    } else {
+        grid = grid < RESIDENT ? RESIDENT : grid > 16 * RESIDENT ? 16 * RESIDENT : grid / RESIDENT * RESIDENT;
+        if (grid > (total + 1) / 2) grid = (total + 1) / 2;
+    }
     // one of the two instantiations works (the range check's flag), the other exits
-    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, false>), dim3((unsigned)grid), dim3(256), 0, st, p, (int)K, total);
-    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, true>), dim3((unsigned)grid), dim3(256), 0, st, p, (int)K, total);
+    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, false>), dim3((unsigned)grid), dim3(256), 0, st, p, (int)K, (int)S, total);
+    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, true>), dim3((unsigned)grid), dim3(256), 0, st, p, (int)K, (int)S, total);
 }
 
 template <int NT, int RR>
