@@ -184,12 +184,12 @@ int tp_bin(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int3
  * (code under HIP graph capture, fixed-memory serving loops): the same
  * arguments, outputs and results, but the launch tables, the exact tier's
  * counters and its deferral list live in a file-scope device array of the
- * library (32 MiB + 4 KiB, held on each device it runs on until the process
+ * library (33 MiB + 8 KiB, held on each device it runs on until the process
  * ends), and no hipMalloc, hipFree or other allocating call is made.
  *   Limits per call: ev->n <= 2^22 events (larger samples: call once per chunk;
  *   counts accumulate) and at most 384 doubles of edge data (a MASS axis takes
  *   3 (nbins + 1), the others nbins + 1); beyond them TP_ERANGE, nothing enqueued.
- *   Launch shape: fixed (256 threads, 8 workgroups per compute unit).
+ *   Launch shape: the default one for the size.
  *   Every call on one device shares the array and overwrites it at its start:
  *   calls that overlap on one device (several streams or threads) race, and
  *   must be ordered by the caller.

@@ -42,6 +42,26 @@ __global__ __launch_bounds__(64) void tp_exact_kernel(const KParams kp)
 {
     const uint32_t cnt = __atomic_load_n(kp.xcount, __ATOMIC_RELAXED);
     const uint32_t n = cnt < kp.xcap ? cnt : kp.xcap;
+    // fold the pass's replicated counters into the samples' and clear them
+    for (int f = blockIdx.x; f < kp.nfold; f += gridDim.x) {
+        const uint32_t item = kp.fold ? kp.fold[f] : (uint32_t)f;
+        const KSample &S = kp.samples[kp.fold ? item >> 8 : 0];
+        const int nrow = (S.nbtot + 1) * 4;
+        const int w = (int)(item & 255u) * FOLD + (int)threadIdx.x;
+        if (S.rep_off < 0 || w >= rep_words(S.nbtot)) continue;
+        uint64_t *copy = kp.rep + S.rep_off + w;
+        const int stride = rep_stride(S.nbtot), n = S.rep_mask + 1;
+        uint64_t v[MAXREP], sum = 0;   // every copy's load in flight at once
+#pragma unroll
+        for (int r = 0; r < MAXREP; ++r) v[r] = r < n ? copy[(int64_t)r * stride] : 0;
+#pragma unroll
+        for (int r = 0; r < MAXREP; ++r) {
+            sum += v[r];
+            if (v[r]) copy[(int64_t)r * stride] = 0;
+        }
+        uint64_t *to = w < nrow ? (S.counts ? S.counts + w : nullptr) : S.stats + (w - nrow);
+        if (sum && to) atomicAdd((unsigned long long *)to, (unsigned long long)sum);
+    }
     for (uint32_t it = blockIdx.x * blockDim.x + threadIdx.x; it < n; it += gridDim.x * blockDim.x) {
         const uint64_t ent = kp.xlist[it];
         const int s = (int)((ent >> 40) & 0xfffff);

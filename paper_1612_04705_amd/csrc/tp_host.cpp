@@ -55,12 +55,12 @@ constexpr uint64_t XCAP_MIN = 1u << 16;
 constexpr uint64_t XCAP_MAX = 1ull << 31;
 constexpr int EXACT_GRID = 128;
 
-// Workgroups of the exact-tier launch (64 threads each, one listed event per
-// thread and pass over the list): more for larger launches, whose lists are
-// longer.
-int exact_grid(int64_t vtotal)
+// Workgroups of the exact-tier launch (64 threads each, one listed event or
+// one counter of the fold per thread and pass): more for larger launches, whose
+// lists are longer, and for more counters.
+int exact_grid(int64_t vtotal, int nfold)
 {
-    return (int)std::min<int64_t>(EXACT_GRID, std::max<int64_t>(16, vtotal >> 16));
+    return (int)std::min<int64_t>(EXACT_GRID, std::max<int64_t>(std::max(16, nfold), vtotal >> 16));
 }
 constexpr size_t MAX_PLANS = 256;        // launch plans kept per device
 constexpr size_t LDS_LIMIT = 64 * 1024;
@@ -76,10 +76,11 @@ uint64_t fnv(const void *p, size_t n, uint64_t h = 1469598103934665603ull)
 }
 
 struct Workspace {
-    void *buf = nullptr;   // xlist | xcount | xdone
+    void *buf = nullptr;   // xlist | xcount | xdone | rep
     uint64_t *xlist = nullptr;
     uint32_t *xcount = nullptr;
     uint32_t *xdone = nullptr;
+    uint64_t *rep = nullptr;   // replicated counters
     uint64_t cap = 0;      // list entries
 };
 
@@ -113,6 +114,8 @@ struct Plan {
     hipStream_t made_on = nullptr;
     KSample *dsamples = nullptr;
     double *dedges = nullptr;
+    std::vector<uint32_t> hfold; // work items of the counter fold
+    uint32_t *dfold = nullptr;
     // the latest enqueued work that reads the plan (a use on another stream
     // first waits for it, so this event covers every earlier use)
     hipEvent_t last_use = nullptr;
@@ -185,13 +188,14 @@ Device &device(int id)
 // A deferral workspace of ``cap`` list entries; its counters are cleared on ``st``.
 int new_workspace(uint64_t cap, hipStream_t st, Workspace &w)
 {
-    const size_t bytes = cap * sizeof(uint64_t) + 64;
+    const size_t bytes = cap * sizeof(uint64_t) + 256 + REP_WORDS * sizeof(uint64_t);
     if (hipMalloc(&w.buf, bytes) != hipSuccess) return fail(TP_ENOMEM, "workspace allocation failed");
     w.cap = cap;
     w.xlist = static_cast<uint64_t *>(w.buf);
     w.xcount = reinterpret_cast<uint32_t *>(static_cast<char *>(w.buf) + cap * sizeof(uint64_t));
     w.xdone = w.xcount + 1;
-    TP_HIP(hipMemsetAsync(w.xcount, 0, 64, st));
+    w.rep = reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(w.xcount) + 256);
+    TP_HIP(hipMemsetAsync(w.xcount, 0, 256 + REP_WORDS * sizeof(uint64_t), st));
     return TP_OK;
 }
 
@@ -429,6 +433,7 @@ void fill_sample(KSample &k, const tp_events &ev, const tp_channel &ch, const tp
     int dabc[4] = { D, ch.triple[0], ch.triple[1], ch.triple[2] };
     k.sigma = perm_sign(dabc, 4) * perm_sign(planes, 4);
     // identical pair: kernel slots inv[f], inv[s] are {0, 2} or {1, 3}
+    k.rep_off = -1;
     k.olo = -1;
     k.odir = 1;
     if (idf >= 0) {
@@ -469,6 +474,37 @@ void fill_sample(KSample &k, const tp_events &ev, const tp_channel &ch, const tp
         }
     }
 }
+
+// Copies of sample k's counters in the replica array, of which ``used`` words are
+// taken: one for every REP_EVENTS events up to MAXREP, fewer where the array is
+// nearly full, none for a sample of few workgroups.
+void place_replica(KSample &k, int64_t &used)
+{
+    const int64_t stride = rep_stride(k.nbtot);
+    int r = 1;
+    while (r < MAXREP && r * (int64_t)REP_EVENTS < k.n) r *= 2;
+    while (r > 1 && used + r * stride > REP_WORDS) r /= 2;
+    k.rep_off = -1;
+    k.rep_mask = 0;
+    if (r == 1) return;
+    k.rep_off = (int32_t)used;
+    k.rep_mask = r - 1;
+    used += r * stride;
+}
+
+int fold_items(const KSample &k) { return k.rep_off < 0 ? 0 : (rep_words(k.nbtot) + FOLD - 1) / FOLD; }
+
+// Replicas of every sample of a plan and the work items of their fold.
+void place_replicas(std::vector<KSample> &hs, std::vector<uint32_t> &fold)
+{
+    int64_t used = 0;
+    for (size_t s = 0; s < hs.size(); ++s) {
+        place_replica(hs[s], used);
+        for (int i = 0; i < fold_items(hs[s]); ++i) fold.push_back((uint32_t)(s << 8) | (uint32_t)i);
+    }
+}
+static_assert((rep_words(MAXBINS) + FOLD - 1) / FOLD <= 256, "the fold's item index has 8 bits");
+static_assert(MAXREP * rep_stride(MAXBINS) <= REP_WORDS, "one sample's replicas always fit");
 
 struct Req {
     const tp_events *ev;
@@ -608,10 +644,13 @@ int build_plan(Device &d, const std::vector<Req> &rq, int mode, hipStream_t st, 
         delete p;
         return fail(TP_ERANGE, "too many samples once split at 2^32 bytes per array");
     }
+    place_replicas(p->hs, p->hfold);
     if (p->hedges.empty()) p->hedges.push_back(0.0);
     const size_t sb = p->hs.size() * sizeof(KSample);
     const size_t eb = p->hedges.size() * sizeof(double);
-    const size_t tot = ((sb + 255) & ~size_t(255)) + eb;
+    const size_t fb = p->hfold.size() * sizeof(uint32_t);
+    const size_t eoff = (sb + 255) & ~size_t(255), foff = (eoff + eb + 255) & ~size_t(255);
+    const size_t tot = foff + fb;
     if (hipMalloc(&p->dbuf, tot) != hipSuccess) {
         delete p;
         return fail(TP_ENOMEM, "plan table allocation failed");
@@ -622,9 +661,11 @@ int build_plan(Device &d, const std::vector<Req> &rq, int mode, hipStream_t st, 
         return fail(TP_ENOMEM, "pinned staging allocation failed");
     }
     std::memcpy(p->pinned, p->hs.data(), sb);
-    std::memcpy(static_cast<char *>(p->pinned) + ((sb + 255) & ~size_t(255)), p->hedges.data(), eb);
+    std::memcpy(static_cast<char *>(p->pinned) + eoff, p->hedges.data(), eb);
+    if (fb) std::memcpy(static_cast<char *>(p->pinned) + foff, p->hfold.data(), fb);
     p->dsamples = static_cast<KSample *>(p->dbuf);
-    p->dedges = reinterpret_cast<double *>(static_cast<char *>(p->dbuf) + ((sb + 255) & ~size_t(255)));
+    p->dedges = reinterpret_cast<double *>(static_cast<char *>(p->dbuf) + eoff);
+    p->dfold = reinterpret_cast<uint32_t *>(static_cast<char *>(p->dbuf) + foff);
     TP_HIP(hipMemcpyAsync(p->dbuf, p->pinned, tot, hipMemcpyHostToDevice, st));
     TP_HIP(hipEventCreateWithFlags(&p->ready, hipEventDisableTiming));
     TP_HIP(hipEventCreateWithFlags(&p->last_use, hipEventDisableTiming));
@@ -644,12 +685,24 @@ int build_plan(Device &d, const std::vector<Req> &rq, int mode, hipStream_t st, 
     return TP_OK;
 }
 
-void defaults(tp_tuning &t)
+// Fills the unset fields of a launch shape for a launch over nv virtual events
+// with a histogram of ``stride`` counters.  Workgroups per CU: 4 (the number
+// that is resident) up to 4e6 events, where a second round of workgroups would
+// cost more in set-up than it evens out (1e6 events |Phi|: 18.0 us with 4, 19.9
+// with 8, 24.5 with 16), 8 up to 2e7 (1e7 |Phi| x mass: 131, 121, 122 us) and 16
+// beyond (1e8 |Phi| x mass: 1193, 1145, 1127 us; |Phi|: 1088, 1064, 1035).
+// Where a histogram has thousands of counters to clear and flush (32 x 32 mass
+// bins: 4108), fewer and larger ranges: 2, 8 and 16 with the upper bound at 4e7
+// (1e6 events: 25.5 us with 2, 36.5 with 4; 3e7: 338 us with 8, 346 with 16),
+// and one LDS copy instead of one per wave (1e6: 25.5 against 27.1 us).
+void defaults(tp_tuning &t, int64_t nv, int stride)
 {
+    const bool wide = stride > 1024;
     if (t.block != 256 && t.block != 512) t.block = 256;
-    if (t.wg_per_cu < 1 || t.wg_per_cu > 32) t.wg_per_cu = 4;
+    if (t.wg_per_cu < 1 || t.wg_per_cu > 32)
+        t.wg_per_cu = nv < 4000000 ? (wide ? 2 : 4) : nv < (wide ? 40000000 : 20000000) ? 8 : 16;
     const int waves = t.block / 64;
-    if (t.lds_copies < 1 || t.lds_copies > waves) t.lds_copies = waves;
+    if (t.lds_copies < 1 || t.lds_copies > waves) t.lds_copies = wide ? 1 : waves;
     if (t.unroll != 1 && t.unroll != 2 && t.unroll != 4) t.unroll = 1;
 }
 
@@ -683,7 +736,7 @@ int side_streams(Device &d)
 int launch_group(int cus, const Group &g, tp_tuning tu, int dtype, int prec, int mode, KParams kp, hipStream_t st)
 {
     const int64_t nv = g.vend - g.vbeg;
-    defaults(tu);
+    defaults(tu, nv, g.hist_stride);
     const int epl = dtype == TP_F32 ? tu.unroll : std::min(tu.unroll, 2);
     const int64_t tile = (int64_t)epl * tu.block;
     int copies = tu.lds_copies;
@@ -740,6 +793,9 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
     kp.xdone = ws.xdone;
     kp.xcap = (uint32_t)ws.cap;
     kp.mode = mode;
+    kp.rep = ws.rep;
+    kp.fold = p.hs.size() > 1 ? p.dfold : nullptr;
+    kp.nfold = (int32_t)p.hfold.size();
     // Several scheme groups run as parallel branches (the caller's stream and
     // NSIDE side streams, in turn): their launches overlap,
     // so one kernel's last workgroups share the chip with the next kernel's
@@ -814,7 +870,7 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
                          (long long)(lst[k] & ((1ull << 40) - 1)), (int)(lst[k] >> 60));
         std::fprintf(stderr, "\n");
     }
-    TP_HIP(launch_exact(p.dtype, mode, kp, exact_grid(p.vtotal), st));
+    TP_HIP(launch_exact(p.dtype, mode, kp, exact_grid(p.vtotal, kp.nfold), st));
     return TP_OK;
 }
 
@@ -909,7 +965,7 @@ std::vector<tp_tuning> resolve_tunings(Device &d, const Plan &p, const std::vect
             auto it = d.tuned.find(group_key(p, p.groups[g], prec));
             if (it != d.tuned.end()) t = it->second;
         }
-        defaults(t);
+        defaults(t, p.groups[g].vend - p.groups[g].vbeg, p.groups[g].hist_stride);
         out[g] = t;
     }
     return out;
@@ -1105,6 +1161,8 @@ int tp_bin_noalloc(const tp_events *ev, const tp_channel *ch, const tp_binning *
     fill_sample(k, *ev, *ch, bn, counts, stats, nullptr, nullptr, ed);
     if (ed.overflow) return fail(TP_ERANGE, "tp_bin_noalloc holds at most 384 doubles of edge data per call");
     k.vstart = 0;
+    int64_t rep_used = 0;
+    place_replica(k, rep_used);
     Group g;
     g.k0 = k.kind[0];
     g.k1 = k.kind[1];
@@ -1121,7 +1179,7 @@ int tp_bin_noalloc(const tp_events *ev, const tp_channel *ch, const tp_binning *
     unsigned char *base = nullptr;
     TP_HIP(noalloc_scratch(dev, &base));
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    TP_HIP(launch_noalloc_setup(k, ed.v, ed.n, base, st));
+    TP_HIP(launch_noalloc_setup(k, ed.v, ed.n, rep_used, base, st));
     KParams kp;
     std::memset(&kp, 0, sizeof kp);
     kp.samples = reinterpret_cast<const KSample *>(base + NA_SAMPLE_OFF);
@@ -1131,14 +1189,12 @@ int tp_bin_noalloc(const tp_events *ev, const tp_channel *ch, const tp_binning *
     kp.xdone = kp.xcount + 1;
     kp.xcap = (uint32_t)NA_MAX_EVENTS;
     kp.mode = 0;
-    tp_tuning tu;
-    tu.block = 256;
-    tu.wg_per_cu = 8;
-    tu.lds_copies = 4;
-    tu.unroll = 1;
+    kp.rep = reinterpret_cast<uint64_t *>(base + NA_REP_OFF);
+    kp.nfold = fold_items(k);
+    const tp_tuning tu{};   // the default shape
     rc = launch_group(cus > 0 ? cus : 256, g, tu, ev->dtype, precision, 0, kp, st);
     if (rc) return rc;
-    TP_HIP(launch_exact(ev->dtype, 0, kp, exact_grid(g.vend), st));
+    TP_HIP(launch_exact(ev->dtype, 0, kp, exact_grid(g.vend, kp.nfold), st));
     return TP_OK;
 }
 
@@ -1210,7 +1266,7 @@ int tp_autotune(const tp_sample *samples, int32_t nsamples, int32_t precision, v
     }
     if (!any_events) {   // nothing to time: the default shape
         tp_tuning t{};
-        defaults(t);
+        defaults(t, 0, 0);
         *best = t;
         return TP_OK;
     }

@@ -38,7 +38,24 @@ struct KSample {
     double guess_inv[2];      // MASS: 1 / bin width
     int32_t olo;              // identical particles in kernel slots olo, olo + 2 (olo 0 or 1; -1: none)
     int32_t odir;             // +1: the faster goes to kernel slot olo, -1: to olo + 2
+    int32_t rep_off;          // replicated counters: offset (words) in the launch's replica array, -1: none
+    int32_t rep_mask;         // number of replicas - 1 (a power of two)
 };
+
+// Replicated counters.  Every workgroup ends a segment by adding its histogram to
+// the sample's counters, at the same addresses as all others of the sample: such
+// device-scope atomics serialise at about 25 ns each, and equal workgroups end
+// together (3e5 events, 20 + 8 counters: 256 workgroups 16.5 us, 586 24 us, 1172
+// 39 us).  So a sample of more than a few workgroups gets up to MAXREP copies of
+// its counters in the launch's replica array; workgroup b adds to copy
+// b & rep_mask, and the exact-tier kernel, which follows every pass, folds the
+// copies into the counters and leaves them zero for the next launch.  One copy
+// holds the (nbtot + 1) * 4 counts, then the NSTAT statistics.
+enum { MAXREP = 32, REP_EVENTS = 4096 };      // a copy for every REP_EVENTS events, up to MAXREP
+constexpr int64_t REP_WORDS = int64_t(1) << 19;     // words of a workspace's replica array (4 MiB)
+constexpr int FOLD = 64;                      // counters per work item of the fold
+constexpr int rep_words(int nbtot) { return (nbtot + 1) * 4 + NSTAT; }
+constexpr int rep_stride(int nbtot) { return (rep_words(nbtot) + 15) & ~15; }   // whole 128-byte lines
 
 // Launch parameters (kernel argument).  One pass launch covers the samples
 // [sbeg, send) -- all of one binning scheme -- whose virtual events are
@@ -57,6 +74,9 @@ struct KParams {
     uint32_t *xcount;         // number of listed events
     uint32_t *xdone;          // finished exact-tier workgroups (last one resets)
     uint32_t xcap;
+    uint64_t *rep;            // replica array (zero between launches)
+    const uint32_t *fold;     // work items of the fold: sample << 8 | item of the sample (null: one sample)
+    int32_t nfold;
 };
 
 // Edge data layout per axis (at eoff):

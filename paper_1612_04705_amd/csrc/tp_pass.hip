@@ -714,6 +714,19 @@ __device__ __forceinline__ T ldnt(const void *base, uint32_t i)
 
 typedef const __attribute__((address_space(4))) KSample *ctab;
 
+// The launch parameters where they lie (the kernel's argument segment), behind an
+// empty asm: what is read through it is read there, by scalar loads, instead of
+// being held in scalar registers from the kernel's start.  The event loop needs
+// those registers: every one it has not got costs a lane read (a vector
+// instruction) per use.
+typedef const __attribute__((address_space(4))) KParams *kptr;
+__device__ __forceinline__ kptr params()
+{
+    kptr k = (kptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return k;
+}
+
 // Load EPL consecutive events per lane, the lane's first at segment offset
 // ``off``, from the 16 component arrays and the tag array.  Every offset is
 // clamped to ``last`` (the segment's last event), so every load stays in
@@ -812,7 +825,7 @@ constexpr bool lean_pass()
 // One tile: EPL consecutive events per lane, the lane's first at segment
 // offset ``loc``; ``len`` events in the segment, which starts at event ev0.
 template <typename Tin, int PREC, int MODE, int EPL, int K0, int K1, bool ORD>
-__device__ __forceinline__ void process_tile(const KParams &kp, int s, const SegIO &io, const Seg &g,
+__device__ __forceinline__ void process_tile(int s, const SegIO &io, const Seg &g,
                                              const Tin (&q)[EPL][4][4], const int (&tg)[EPL], uint32_t loc,
                                              uint32_t len, int64_t ev0, uint32_t *myhist, int srow,
                                              WaveCounts &wc)
@@ -852,9 +865,10 @@ __device__ __forceinline__ void process_tile(const KParams &kp, int s, const Seg
         }
         bool listed = false, unres = false;
         if (o.cls == CLS_DEFER) {
-            const uint32_t slot = atomicAdd(kp.xcount, 1u);
-            if (slot < kp.xcap) {
-                kp.xlist[slot] = ((uint64_t)o.why << 60) | ((uint64_t)s << 40) | (uint64_t)(ev0 + li);
+            const kptr kp = params();
+            const uint32_t slot = atomicAdd(kp->xcount, 1u);
+            if (slot < kp->xcap) {
+                kp->xlist[slot] = ((uint64_t)o.why << 60) | ((uint64_t)s << 40) | (uint64_t)(ev0 + li);
                 listed = true;
             } else {
                 unres = true;
@@ -906,7 +920,7 @@ constexpr bool prefetch_tiles()
 // The event loop of one segment: ``len`` events of sample s from event ev0,
 // addressed by 32-bit offsets (the host caps a workgroup's range).
 template <typename Tin, int PREC, int MODE, int EPL, int K0, int K1, bool ORD>
-__device__ __forceinline__ void run_segment(const KParams &kp, int s, const SegIO &io, const Seg &g,
+__device__ __forceinline__ void run_segment(int s, const SegIO &io, const Seg &g,
                                             int64_t ev0, uint32_t len, uint32_t *myhist, int srow,
                                             WaveCounts &wc)
 {
@@ -926,10 +940,10 @@ __device__ __forceinline__ void run_segment(const KParams &kp, int s, const SegI
         for (uint32_t t0 = 0; t0 < len; t0 += 2 * step) {
             const uint32_t t1 = t0 + step;
             load_scalar<Tin, 1>(io.S, ev0, t1 + lane0, last, qb, tb);
-            process_tile<Tin, PREC, MODE, 1, K0, K1, ORD>(kp, s, io, g, qa, ta, t0 + lane0, len, ev0, myhist, srow, wc);
+            process_tile<Tin, PREC, MODE, 1, K0, K1, ORD>(s, io, g, qa, ta, t0 + lane0, len, ev0, myhist, srow, wc);
             if (t1 >= len) break;
             load_scalar<Tin, 1>(io.S, ev0, t1 + step + lane0, last, qa, ta);
-            process_tile<Tin, PREC, MODE, 1, K0, K1, ORD>(kp, s, io, g, qb, tb, t1 + lane0, len, ev0, myhist, srow, wc);
+            process_tile<Tin, PREC, MODE, 1, K0, K1, ORD>(s, io, g, qb, tb, t1 + lane0, len, ev0, myhist, srow, wc);
         }
         return;
     }
@@ -946,12 +960,12 @@ __device__ __forceinline__ void run_segment(const KParams &kp, int s, const SegI
             for (uint32_t t = 0; t < nfull; t += 2) {
                 const uint32_t n1 = t + 1 < nfull ? t + 1 : nfull - 1;
                 load_vector<Tin, EPL>(io.S, ev0, n1 * step + lane0, qb, tb);
-                process_tile<Tin, PREC, MODE, EPL, K0, K1, ORD>(kp, s, io, g, qa, ta, t * step + lane0, len, ev0, myhist,
+                process_tile<Tin, PREC, MODE, EPL, K0, K1, ORD>(s, io, g, qa, ta, t * step + lane0, len, ev0, myhist,
                                                            srow, wc);
                 if (t + 1 >= nfull) break;
                 const uint32_t n2 = t + 2 < nfull ? t + 2 : nfull - 1;
                 load_vector<Tin, EPL>(io.S, ev0, n2 * step + lane0, qa, ta);
-                process_tile<Tin, PREC, MODE, EPL, K0, K1, ORD>(kp, s, io, g, qb, tb, (t + 1) * step + lane0, len, ev0,
+                process_tile<Tin, PREC, MODE, EPL, K0, K1, ORD>(s, io, g, qb, tb, (t + 1) * step + lane0, len, ev0,
                                                            myhist, srow, wc);
             }
         }
@@ -960,7 +974,7 @@ __device__ __forceinline__ void run_segment(const KParams &kp, int s, const SegI
             Tin q[EPL][4][4];
             int tg[EPL];
             load_vector<Tin, EPL>(io.S, ev0, t * step + lane0, q, tg);
-            process_tile<Tin, PREC, MODE, EPL, K0, K1, ORD>(kp, s, io, g, q, tg, t * step + lane0, len, ev0, myhist, srow,
+            process_tile<Tin, PREC, MODE, EPL, K0, K1, ORD>(s, io, g, q, tg, t * step + lane0, len, ev0, myhist, srow,
                                                        wc);
         }
     }
@@ -968,7 +982,7 @@ __device__ __forceinline__ void run_segment(const KParams &kp, int s, const SegI
         Tin q[EPL][4][4];
         int tg[EPL];
         load_scalar<Tin, EPL>(io.S, ev0, t0 + lane0, last, q, tg);
-        process_tile<Tin, PREC, MODE, EPL, K0, K1, ORD>(kp, s, io, g, q, tg, t0 + lane0, len, ev0, myhist, srow, wc);
+        process_tile<Tin, PREC, MODE, EPL, K0, K1, ORD>(s, io, g, q, tg, t0 + lane0, len, ev0, myhist, srow, wc);
     }
 }
 
@@ -976,36 +990,45 @@ __device__ __forceinline__ void run_segment(const KParams &kp, int s, const SegI
 // each workgroup takes a contiguous range of the virtual event space, splits
 // it at sample boundaries, counts into LDS and flushes every segment.
 template <typename Tin, int PREC, int MODE, int EPL, int K0, int K1, bool ORD>
-__global__ __launch_bounds__(512) void tp_pass_kernel(const KParams kp)
+__global__ __launch_bounds__(512) void tp_pass_kernel(const KParams)
 {
     constexpr bool BINNED = MODE == 0 && K0 != AX_NONE;
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *tot = reinterpret_cast<uint32_t *>(smem);          // 8 words: class totals, out of range
     uint32_t *hist = tot + 8;
-    const int hist_words = kp.lds_copies * kp.hist_stride;
+    const kptr kp = params();
+    const int copies = kp->lds_copies, hist_stride = kp->hist_stride;
+    const int hist_words = copies * hist_stride;
     double *ecache = reinterpret_cast<double *>(smem + (((8 + hist_words) * 4 + 15) & ~15));
     const int tid = threadIdx.x;
     const int nthr = blockDim.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    uint32_t *myhist = hist + (wave % kp.lds_copies) * kp.hist_stride;
+    uint32_t *myhist = hist + (wave % copies) * hist_stride;
 
-    int64_t vbeg = kp.vbeg + (int64_t)blockIdx.x * kp.range;
-    const int64_t vend = vbeg + kp.range < kp.vend ? vbeg + kp.range : kp.vend;
-    if (vbeg >= vend) return;
+    // the end of this workgroup's range, which starts at vbeg
+    auto range_end = [](kptr k) {
+        const int64_t end = k->vbeg + ((int64_t)blockIdx.x + 1) * k->range;
+        return end < k->vend ? end : k->vend;
+    };
+    int64_t vbeg = kp->vbeg + (int64_t)blockIdx.x * kp->range;
+    if (vbeg >= range_end(kp)) return;
     // the sample table is read-only for the whole launch: read it through the
     // constant address space, so its fields arrive by scalar loads
-    const ctab samples = (ctab)kp.samples;
-    int lo = kp.sbeg, hi = kp.send - 1;
+    const ctab samples = (ctab)kp->samples;
+    int lo = kp->sbeg, hi = kp->send - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (samples[mid].vstart <= vbeg) lo = mid;
         else hi = mid - 1;
     }
-    for (int s = lo; s < kp.send && vbeg < vend; ++s) {
-        const ctab S = samples + s;
+    for (int s = lo;; ++s) {
+        const kptr ks = params();
+        const int64_t vend = range_end(ks);
+        if (!(s < ks->send && vbeg < vend)) break;
+        const ctab S = (ctab)ks->samples + s;
         const int64_t sv0 = S->vstart;
-        const int64_t sv1 = s + 1 < kp.send ? samples[s + 1].vstart : kp.vend;
+        const int64_t sv1 = s + 1 < ks->send ? S[1].vstart : ks->vend;
         if (sv1 <= vbeg) continue;
         const int64_t segend = vend < sv1 ? vend : sv1;
         const int64_t n = S->n;
@@ -1020,8 +1043,6 @@ __global__ __launch_bounds__(512) void tp_pass_kernel(const KParams kp)
         io.vec = S->vec != 0;
         io.cls_out = S->cls_out;
         io.ct_out = S->ct_out;
-        uint64_t *counts = S->counts;
-        uint64_t *stats = S->stats;
         Seg g;
         g.sigma = S->sigma;
         g.nb0 = S->nbins[0];
@@ -1043,12 +1064,12 @@ __global__ __launch_bounds__(512) void tp_pass_kernel(const KParams kp)
         g.e0 = ecache;
         g.e1 = ecache + nd0;
         for (int i = tid; i < 8 + hist_words; i += nthr) tot[i] = 0;   // tot and hist are contiguous
-        for (int i = tid; i < nd0; i += nthr) ecache[i] = kp.edges[eoff0 + i];
-        for (int i = tid; i < nd1; i += nthr) ecache[nd0 + i] = kp.edges[eoff1 + i];
+        for (int i = tid; i < nd0; i += nthr) ecache[i] = ks->edges[eoff0 + i];
+        for (int i = tid; i < nd1; i += nthr) ecache[nd0 + i] = ks->edges[eoff1 + i];
         __syncthreads();
 
         WaveCounts wc = { 0, 0, 0, 0 };
-        run_segment<Tin, PREC, MODE, EPL, K0, K1, ORD>(kp, s, io, g, ev0, (uint32_t)(ev1 - ev0), myhist, srow, wc);
+        run_segment<Tin, PREC, MODE, EPL, K0, K1, ORD>(s, io, g, ev0, (uint32_t)(ev1 - ev0), myhist, srow, wc);
         if (!BINNED && MODE == 0 && lane == 0) {
             atomicAdd(&myhist[0], wc.c0);
             atomicAdd(&myhist[1], wc.c1);
@@ -1056,15 +1077,27 @@ __global__ __launch_bounds__(512) void tp_pass_kernel(const KParams kp)
             atomicAdd(&myhist[3], wc.c3);
         }
         __syncthreads();
-        // fold the copies; bin rows also feed the class totals, the overflow
+        // the sample's counters, or this workgroup's copy of them (read here, not
+        // ahead of the event loop)
+        const kptr kf = params();
+        ctab F = (ctab)kf->samples + s;
+        asm volatile("" : "+s"(F));
+        uint64_t *counts = F->counts;
+        uint64_t *stats = F->stats;
+        if (F->rep_off >= 0) {
+            uint64_t *copy = kf->rep + F->rep_off + (int64_t)((int)blockIdx.x & F->rep_mask) * rep_stride(F->nbtot);
+            counts = copy;
+            stats = copy + (F->nbtot + 1) * 4;
+        }
+        // fold the histogram copies; bin rows also feed the class totals, the overflow
         // row the totals and the out-of-range count
         for (int i = tid; i < srow + NSTAT; i += nthr) {
             uint32_t v = 0;
-            for (int k = 0; k < kp.lds_copies; ++k) v += hist[k * kp.hist_stride + i];
+            for (int k = 0; k < copies; ++k) v += hist[k * hist_stride + i];
             if (i < srow) {
                 if (BINNED && i >= 4 && v) atomicAdd(&tot[i & 3], v);
                 if (BINNED && i >= nrow && v) atomicAdd(&tot[4], v);
-                if (i < nrow && v && counts && (!BINNED || i >= 4))
+                if (MODE == 0 && i < nrow && v && counts && (!BINNED || i >= 4))
                     atomicAdd((unsigned long long *)(counts + i), (unsigned long long)v);
             } else if (i - srow == ST_EVENTS) {
                 atomicAdd((unsigned long long *)(stats + ST_EVENTS), (unsigned long long)(ev1 - ev0));

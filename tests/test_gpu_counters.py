@@ -1,0 +1,81 @@
+"""Replicated counters of the pass: samples around the sizes at which a sample gets 1, 2, ... 32 copies of its
+counters, with few and with the most bins, alone, in a batch whose copies do not all fit, graphed and replayed, and
+with the launch shapes between which the default changes.  Counts are integers: they equal the oracle's, or for a
+sample stored twice over, twice the sample's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1612_04705_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tp():
+    from paper_1612_04705_amd import tpasym
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    tpasym.load()
+    return tpasym
+
+
+def table(bn, counts):
+    c = [int(v) for v in counts.cpu().numpy().view(np.uint64)]
+    return [c[4 * r:4 * r + 4] for r in range(bn.nrows)]
+
+
+D0 = synth.CHANNELS["D0_KKpipi"]
+WIDE = [synth.mass_axis((0, 1), 2 * synth.M_K, synth.M_D0 - 2 * synth.M_PI, 32),
+        synth.mass_axis((2, 3), 2 * synth.M_PI, synth.M_D0 - 2 * synth.M_K, 32)]
+
+
+@pytest.mark.parametrize("axes", [[], [synth.absphi_axis(10)], WIDE], ids=["global", "phi", "1024 bins"])
+@pytest.mark.parametrize("n", [4096, 4097, 8193, 131073, 200003])
+def test_sizes(tp, axes, n):
+    s = synth.generate(D0, n, 700 + n)
+    comps, tag = s.numpy()
+    want = oracle.run(comps, tag, D0.triple, D0.planes, axes)
+    ds, bn, ch = tp.DeviceSample.from_sample(s), tp.Binning(axes), tp.channel(D0.triple, D0.planes)
+    counts, stats = tp.new_counts(bn)
+    for k, call in enumerate((tp.bin, tp.bin_noalloc, tp.bin)):     # counts accumulate; the copies start clean each time
+        call(ds, ch, bn, tp.TP_PREC_F32_RECHECK, counts, stats)
+        assert table(bn, counts) == [[(k + 1) * v for v in row] for row in want["counts"]]
+        assert [int(v) for v in stats[:4].cpu()] == [(k + 1) * v for v in want["stats"]]
+    _, _, st = tp.compute(ds, ch, tp.TP_PREC_F64, want_ct=False)
+    assert [int(v) for v in st[:3].cpu()] == want["stats"][:3]
+
+
+def test_batch_beyond_the_replica_array(tp):
+    """20 samples of 1024 bins, 32 copies of 4112 words each: the array holds the copies of three, half the
+    copies of the next, ..., and the last samples count directly."""
+    n = 140001
+    s = synth.generate(D0, n, 800)
+    comps, tag = s.numpy()
+    want = oracle.run(comps, tag, D0.triple, D0.planes, WIDE)
+    ds, bn, ch = tp.DeviceSample.from_sample(s), tp.Binning(WIDE), tp.channel(D0.triple, D0.planes)
+    buf = torch.zeros((20, bn.nrows * 4), dtype=torch.int64, device="cuda")
+    stats = torch.zeros((20, 8), dtype=torch.int64, device="cuda")
+    b = tp.Batch([(ds, ch, bn, buf[i], stats[i]) for i in range(20)])
+    for k, graph in enumerate((False, True, True, True)):
+        b.run(tp.TP_PREC_F32_RECHECK, graph=graph, check=True)
+        for i in range(20):
+            assert table(bn, buf[i]) == [[(k + 1) * v for v in row] for row in want["counts"]], (k, i)
+            assert [int(v) for v in stats[i, :4].cpu()] == [(k + 1) * v for v in want["stats"]]
+
+
+@pytest.mark.parametrize("copies", [1, 2])
+def test_default_shapes(tp, copies):
+    """Around 4e6 events, where the default launch shape changes: a 2^21-event sample once and twice over."""
+    axes = [synth.absphi_axis(10)]
+    s = synth.generate(D0, 1 << 21, 900, device="cuda")
+    bn, ch = tp.Binning(axes), tp.channel(D0.triple, D0.planes)
+    part = tp.DeviceSample.from_sample(s)
+    small, st = tp.new_counts(bn)
+    for e0 in range(0, 1 << 21, 1 << 18):
+        tp.bin(tp.DeviceSample([c[e0:e0 + (1 << 18)] for c in part.comps], part.tag[e0:e0 + (1 << 18)]), ch, bn,
+               tp.TP_PREC_F64, small, st)
+    ds = tp.DeviceSample([c.repeat(copies) for c in part.comps], part.tag.repeat(copies))
+    for call in (tp.bin, tp.bin_noalloc):
+        counts, stats = call(ds, ch, bn, tp.TP_PREC_F32_RECHECK)
+        assert torch.equal(counts, copies * small) and torch.equal(stats[:4], copies * st[:4])
