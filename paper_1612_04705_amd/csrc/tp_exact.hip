@@ -36,6 +36,144 @@ __device__ __forceinline__ int order_f64(const double (&x)[4][4], int lo)
     return sv > 0.0 ? 1 : -1;
 }
 
+// ------------------------------------------------- double words on 16 lanes
+// tpw::decide_dw of one event by a group of 16 lanes.  A listed event's
+// decisions are a chain of some 7,700 dependent float64 instructions on one lane,
+// about 20 us however few events there are, and a launch that lists any waits
+// for it.  Here lane l = 4 a + b of the group forms the quantities of its own
+// index -- P_b, the products p_a.p_b, G_ab, one Laplace term, one square, every
+// 16th edge -- and the lanes exchange them, which leaves about a seventh of the
+// chain.  The values are the same invariants with the same running bounds (only
+// the order of some sums differs, and each sum carries its own bound), so every
+// decision it certifies is the exact one.
+using tpw::V;
+
+__device__ __forceinline__ V vget(const V &x, int src)      // x of lane src of the wave
+{
+    return V{ { __shfl(x.v.hi, src), __shfl(x.v.lo, src) }, __shfl(x.e, src) };
+}
+
+__device__ __forceinline__ V vsum(V x, int lanes)            // sum over aligned runs of ``lanes`` lanes
+{
+    for (int o = 1; o < lanes; o <<= 1)
+        x = tpw::add(x, V{ { __shfl_xor(x.v.hi, o), __shfl_xor(x.v.lo, o) }, __shfl_xor(x.e, o) });
+    return x;
+}
+
+__device__ __forceinline__ double pick(const double (&r)[4], int c)
+{
+    const double lo = c & 1 ? r[1] : r[0], hi = c & 1 ? r[3] : r[2];
+    return c & 2 ? hi : lo;
+}
+
+// The lanes of one group must enter together; ``base`` is its first lane.
+__device__ __forceinline__ int decide_lanes(const double (&x)[4][4], int tag, const KSample &S, int nax,
+                                         const double *const (&edges)[2], int base, int &bin)
+{
+    using namespace tpw;
+    bin = -1;
+    const int l = (int)(threadIdx.x & 15), a = l >> 2, b = l & 3;
+    auto any = [&](bool p) { return ((__ballot(p) >> base) & 0xffffull) != 0; };
+    auto count = [&](bool p) { return __popcll((__ballot(p) >> base) & 0xffffull); };
+    if (tag != 0 && tag != 1) return W_INVALID;
+    double xa[4], xb[4], col[4];                 // rows a and b, column b
+    bool small = true;
+    for (int s = 0; s < 4; ++s) {
+        col[s] = pick(x[s], b);
+        for (int c = 0; c < 4; ++c) {
+            const double m = dabs(x[s][c]);
+            small = small && (m == 0.0 || (m >= 0x1p-30 && m <= 0x1p40));
+        }
+    }
+    if (!small) return W_UNCERTAIN;
+    for (int c = 0; c < 4; ++c) {
+        const double r[4] = { x[0][c], x[1][c], x[2][c], x[3][c] };
+        xa[c] = pick(r, a);
+        xb[c] = pick(r, b);
+    }
+    // P_b; M^2 = P_0^2 - P_1^2 - P_2^2 - P_3^2
+    const V Pb = add(add(add(exact(col[0]), exact(col[1])), exact(col[2])), exact(col[3]));
+    const V Pb2 = mul(Pb, Pb);
+    const V M2 = vsum(b == 0 ? Pb2 : neg(Pb2), 4);
+    const V P0 = vget(Pb, base), P02 = vget(Pb2, base);
+    const int sE = csign(P0), sM = csign(M2);
+    if (any(sE < 0 || sM < 0)) return W_INVALID;
+    if (any(sE == 0 || sM == 0)) return W_UNCERTAIN;
+    // Laplace term l & 7 (6 and 7: none) of det[x0; x1; x2; x3] on row pairs (0,1) | (2,3)
+    V term = exact(0.0);
+    {
+        const int k = l & 7;
+        const int i = k < 3 ? 0 : k < 5 ? 1 : 2, j = k < 3 ? k + 1 : k < 5 ? k - 1 : 3;      // its columns
+        const int m = k < 1 ? 2 : k < 3 ? 1 : 0, n = k == 5 ? 1 : k == 2 || k == 4 ? 2 : 3;       // the other two, in order
+        const V top = sub(prod(pick(x[0], i), pick(x[1], j)), prod(pick(x[0], j), pick(x[1], i)));
+        const V bot = sub(prod(pick(x[2], m), pick(x[3], n)), prod(pick(x[2], n), pick(x[3], m)));
+        const V t = mul(top, bot);
+        if (k < 6) term = (k == 1 || k == 4) ? neg(t) : t;
+    }
+    const int sd = csign(vsum(term, 8)) * S.sigma;
+    if (any(sd == 0)) return W_UNCERTAIN;
+    const int cls = tag == 0 ? (sd > 0 ? W_I : W_II) : (sd < 0 ? W_III : W_IV);
+    if (nax <= 0) return cls;
+
+    const V d = mink(xa, xb);
+    const V PPa = vsum(d, 4);
+    const V PPb = vget(PPa, base + 4 * b);
+    const V G = sub(mul(PPa, PPb), mul(M2, d));
+    int bsum = 0;
+    bool oor = false;
+    for (int ax = 0; ax < nax; ++ax) {
+        const int nb = S.nbins[ax];
+        const double *e = edges[ax];
+        int j = 0;
+        bool bad = false;
+        if (S.kind[ax] == AX_ABSPHI) {
+            // lane b: X = G02 G13 - G03 G12, N1 = G00 G11 - G01^2, N2 = G22 G33 - G23^2
+            const int i0 = b == 0 ? 2 : b == 1 ? 0 : 10, i1 = b == 0 ? 7 : b == 1 ? 5 : 15;
+            const int i2 = b == 0 ? 3 : b == 1 ? 1 : 11, i3 = b == 0 ? 6 : b == 1 ? 1 : 11;
+            const V Z = sub(mul(vget(G, base + i0), vget(G, base + i1)), mul(vget(G, base + i2), vget(G, base + i3)));
+            const V X = vget(Z, base), D = mul(vget(Z, base + 1), vget(Z, base + 2)), X2 = mul(X, X);
+            const int sX = csign(X);
+            for (int k0 = 1; k0 < nb; k0 += 16) {
+                const int k = k0 + l;
+                int le = 0;
+                if (k < nb) le = cos_le(sX, csign(sub(X2, mul(prod(e[k], e[k]), D))), e[k]);
+                bad = bad || any(le < 0);
+                j += count(le > 0);
+            }
+        } else if (S.kind[ax] == AX_ABSCOS) {
+            const int s = S.slots[ax];
+            const double r[4] = { x[0][0], x[1][0], x[2][0], x[3][0] };
+            const V Nn = sub(mul(vget(PPa, base + 4 * s), P0), mul(M2, exact(pick(r, s))));
+            const V AB = mul(vget(G, base + 5 * s), sub(P02, M2)), Nn2 = mul(Nn, Nn);
+            for (int k0 = 1; k0 < nb; k0 += 16) {
+                const int k = k0 + l;
+                int sF = -1;
+                if (k < nb) sF = csign(sub(Nn2, mul(prod(e[k], e[k]), AB)));
+                bad = bad || any(sF == 0);
+                j += count(sF > 0);
+            }
+        } else {
+            V Sb = exact(0.0);
+            for (int t = 0; t < 4; ++t)
+                if (S.slots[ax] & (1 << t)) Sb = add(Sb, exact(col[t]));
+            const V Sb2 = mul(Sb, Sb);
+            const V m2 = vsum(b == 0 ? Sb2 : neg(Sb2), 4);
+            for (int k0 = 0; k0 <= nb; k0 += 16) {
+                const int k = k0 + l;
+                int sF = -1;
+                if (k <= nb) sF = csign(sub(m2, prod(e[k], e[k])));
+                bad = bad || any(sF == 0);
+                j += count(k > 0 && k < nb && sF > 0);
+                oor = oor || any((k == 0 && sF < 0) || (k == nb && sF > 0));
+            }
+        }
+        if (bad) return W_UNCERTAIN;
+        bsum = bsum * nb + j;
+    }
+    bin = oor ? -1 : bsum;
+    return cls;
+}
+
 // ------------------------------------------------------------------ exact tier
 template <typename Tin, int MODE>
 __global__ __launch_bounds__(64) void tp_exact_kernel(const KParams kp)
@@ -62,7 +200,13 @@ __global__ __launch_bounds__(64) void tp_exact_kernel(const KParams kp)
         uint64_t *to = w < nrow ? (S.counts ? S.counts + w : nullptr) : S.stats + (w - nrow);
         if (sum && to) atomicAdd((unsigned long long *)to, (unsigned long long)sum);
     }
-    for (uint32_t it = blockIdx.x * blockDim.x + threadIdx.x; it < n; it += gridDim.x * blockDim.x) {
+    // a list that the launch's groups of 16 lanes take in one go is decided by
+    // groups (3e6 float32 events of a |cos theta| scheme, about 25 listed: the
+    // launch 27 us by lanes, 16 by groups; 64-sample batch, 417 listed: 35 and
+    // 22), a longer one by lanes, which spend half as many instructions per event
+    const bool grouped = n <= gridDim.x * blockDim.x / 16;
+    const uint32_t me = blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint32_t it = grouped ? me / 16 : me; it < n; it += gridDim.x * blockDim.x) {
         const uint64_t ent = kp.xlist[it];
         const int s = (int)((ent >> 40) & 0xfffff);
         const int64_t i = (int64_t)(ent & ((1ull << 40) - 1));
@@ -111,9 +255,12 @@ __global__ __launch_bounds__(64) void tp_exact_kernel(const KParams kp)
             }
         }
         int bin = -1;
-        int cls = order_unres ? (int)CLS_UNRESOLVED
-                : finite ? tpw::decide_dw(xv, tag, S.sigma, nax, S.kind, S.nbins, S.slots, eds, bin)
-                         : (int)tpw::W_UNCERTAIN;
+        int cls;
+        if (order_unres) cls = (int)CLS_UNRESOLVED;
+        else if (!finite) cls = (int)tpw::W_UNCERTAIN;
+        else if (grouped) cls = decide_lanes(xv, tag, S, nax, eds, (int)(threadIdx.x & 48), bin);
+        else cls = tpw::decide_dw(xv, tag, S.sigma, nax, S.kind, S.nbins, S.slots, eds, bin);
+        if (grouped && (threadIdx.x & 15) != 0) continue;      // the group's first lane goes on
         if (cls == tpw::W_UNCERTAIN) {
             int64_t mant[4][4];
             int ex[4][4];

@@ -477,12 +477,13 @@ void fill_sample(KSample &k, const tp_events &ev, const tp_channel &ch, const tp
 
 // Copies of sample k's counters in the replica array, of which ``used`` words are
 // taken: one for every REP_EVENTS events up to MAXREP, fewer where the array is
-// nearly full, none for a sample of few workgroups.
+// nearly full, none for a sample of at most 64 workgroups of 256 events, whose
+// atomics take no longer than the fold (1.3 us).
 void place_replica(KSample &k, int64_t &used)
 {
     const int64_t stride = rep_stride(k.nbtot);
     int r = 1;
-    while (r < MAXREP && r * (int64_t)REP_EVENTS < k.n) r *= 2;
+    while (k.n > 4 * REP_EVENTS && r < MAXREP && r * (int64_t)REP_EVENTS < k.n) r *= 2;
     while (r > 1 && used + r * stride > REP_WORDS) r /= 2;
     k.rep_off = -1;
     k.rep_mask = 0;

@@ -1070,13 +1070,6 @@ __global__ __launch_bounds__(512) void tp_pass_kernel(const KParams)
 
         WaveCounts wc = { 0, 0, 0, 0 };
         run_segment<Tin, PREC, MODE, EPL, K0, K1, ORD>(s, io, g, ev0, (uint32_t)(ev1 - ev0), myhist, srow, wc);
-        if (!BINNED && MODE == 0 && lane == 0) {
-            atomicAdd(&myhist[0], wc.c0);
-            atomicAdd(&myhist[1], wc.c1);
-            atomicAdd(&myhist[2], wc.c2);
-            atomicAdd(&myhist[3], wc.c3);
-        }
-        __syncthreads();
         // the sample's counters, or this workgroup's copy of them (read here, not
         // ahead of the event loop)
         const kptr kf = params();
@@ -1089,6 +1082,13 @@ __global__ __launch_bounds__(512) void tp_pass_kernel(const KParams)
             counts = copy;
             stats = copy + (F->nbtot + 1) * 4;
         }
+        if (!BINNED && MODE == 0 && lane == 0) {
+            atomicAdd(&myhist[0], wc.c0);
+            atomicAdd(&myhist[1], wc.c1);
+            atomicAdd(&myhist[2], wc.c2);
+            atomicAdd(&myhist[3], wc.c3);
+        }
+        __syncthreads();
         // fold the histogram copies; bin rows also feed the class totals, the overflow
         // row the totals and the out-of-range count
         for (int i = tid; i < srow + NSTAT; i += nthr) {

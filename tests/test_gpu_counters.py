@@ -1,4 +1,4 @@
-"""Replicated counters of the pass: samples around the sizes at which a sample gets 1, 2, ... 32 copies of its
+"""Replicated counters of the pass: samples around the sizes at which a sample gets none, 8, ... 32 copies of its
 counters, with few and with the most bins, alone, in a batch whose copies do not all fit, graphed and replayed, and
 with the launch shapes between which the default changes.  Counts are integers: they equal the oracle's, or for a
 sample stored twice over, twice the sample's."""
@@ -31,7 +31,7 @@ WIDE = [synth.mass_axis((0, 1), 2 * synth.M_K, synth.M_D0 - 2 * synth.M_PI, 32),
 
 
 @pytest.mark.parametrize("axes", [[], [synth.absphi_axis(10)], WIDE], ids=["global", "phi", "1024 bins"])
-@pytest.mark.parametrize("n", [4096, 4097, 8193, 131073, 200003])
+@pytest.mark.parametrize("n", [4097, 16384, 16385, 32769, 131073, 200003])
 def test_sizes(tp, axes, n):
     s = synth.generate(D0, n, 700 + n)
     comps, tag = s.numpy()
