@@ -85,7 +85,7 @@ template <int NT, bool SAFE>
 struct Smem {
     static constexpr int C = 32 * NT;
     uint16_t xh[2][JC][XS];             // distance operands of this chunk and the next, float16 slots (see slot())
-    uint16_t gs[C][JC + GPAD];          // columns of the chunk, [c][j], float16 0 or 1
+    uint16_t gs[C][JC + GPAD];          // columns of the chunk, [32 t + col][j], float16 0 or 1
     float cw[4][MAXD];                  // per-wave coordinate sums for the centre c
     float cen[MAXD];                    // the centre c
     double red[C][1 + MAXR];            // workgroup totals
@@ -101,22 +101,48 @@ struct CentreSmem {
     float cen[MAXD];
 };
 
+// Coordinates 0 .. KD - 1 of event i, read without a branch (past either end the
+// last one's), so that the loads are all in flight together.
+template <int KD>
+__device__ __forceinline__ void load_coords(const EParams &p, int64_t i, float (&y)[KD])
+{
+    i = i < p.n ? i : p.n - 1;
+#pragma unroll
+    for (int d = 0; d < KD; ++d) y[d] = p.Y[(d < p.D ? d : p.D - 1) * p.ldY + i];
+}
+
+// x + the x of the lane whose number differs in bit O (a mirrored lane for
+// O = 4, 8: equal, since lanes that differ only in lower bits hold the same sum)
+template <int O>
+__device__ __forceinline__ float add_xor(float x)
+{
+    if constexpr (O >= 16) return x + __shfl_xor(x, O);
+    constexpr int ctrl = O == 1 ? 0xB1 : O == 2 ? 0x4E : O == 4 ? 0x141 : 0x140;
+    return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), ctrl, 0xf, 0xf, false));
+}
+
 // Centre c of the scaled coordinates: the mean of the first min(n, 256)
 // events, formed in a fixed order so that every workgroup gets the same bits.
-template <class SM>
-__device__ __forceinline__ void centre(const EParams &p, SM &sm)
+// y: thread tid's event, coordinates 0 .. KD - 1 (KD >= D).
+template <int KD, class SM>
+__device__ __forceinline__ void centre(const EParams &p, SM &sm, const float (&y)[KD])
 {
     const int tid = threadIdx.x;
     const int64_t m = p.n < 256 ? p.n : 256;
+    float x[KD];
 #pragma unroll
-    for (int d = 0; d < MAXD; ++d) {
-        float x = (d < p.D && tid < m) ? p.Y[d * p.ldY + tid] * p.yscale : 0.0f;
+    for (int d = 0; d < KD; ++d) x[d] = (d < p.D && tid < m) ? y[d] * p.yscale : 0.0f;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) x += __shfl_xor(x, o);
-        if ((tid & 63) == 0) sm.cw[tid >> 6][d] = x;
+    for (int d = 0; d < KD; ++d) x[d] = add_xor<8>(add_xor<4>(add_xor<2>(add_xor<1>(x[d]))));
+#pragma unroll
+    for (int d = 0; d < KD; ++d) x[d] = add_xor<16>(x[d]);
+#pragma unroll
+    for (int d = 0; d < KD; ++d) {
+        x[d] = add_xor<32>(x[d]);
+        if ((tid & 63) == 0) sm.cw[tid >> 6][d] = x[d];
     }
     __syncthreads();
-    if (tid < MAXD)
+    if (tid < KD)
         sm.cen[tid] = ((sm.cw[0][tid] + sm.cw[1][tid]) + (sm.cw[2][tid] + sm.cw[3][tid])) / (float)(m > 0 ? m : 1);
     __syncthreads();
 }
@@ -152,61 +178,81 @@ __device__ __forceinline__ void split16(const float (&x)[KA], uint16_t (&hi)[KA]
     }
 }
 
+template <int N> struct Bytes;
+template <> struct Bytes<1> { typedef uint8_t t; };
+template <> struct Bytes<2> { typedef uint16_t t; };
+template <> struct Bytes<4> { typedef uint32_t t; };
+
+// Columns and lanes.  Lane col (0..31) of product tile t holds column NT col + t,
+// so that a lane's columns are neighbours in G: one load of NT bytes per row.
 // What a lane keeps of its wave's 32 rows of a row block: its row's operand
-// halves, its row's raw coordinates (SAFE), and for the flush, bit r of g[t] the
-// column value G[row][32 t + col] and bit r of w[q] the row weight G[row][q],
-// row = 8 (r / 4) + 4 h + r % 4 (the lane's rows in a product tile).
-template <int NT, int NS, int RR, bool SAFE>
+// halves, its row's raw coordinates (SAFE), and for the flush the column values
+// G[row][NT col + t] in byte t of g[r], row = 8 (r / 4) + 4 h + r % 4 (the lane's
+// rows in a product tile).
+template <int NT, int NS, bool SAFE>
 struct Rows {
     u32x4 xi[2];
     float y[SAFE ? 2 * NS - 2 : 1];
-    uint32_t g[NT];
-    uint32_t w[RR];
+    uint32_t g[16];
     bool far;           // SAFE: a row of the block is outside the matrix-core range
 };
 
 // Row block setup, each wave for itself: rows ib .. ib + 31, the wave's share of
-// the block of ROWS rows that starts at block0.  This lane's row vector is
-// x_i = (-2 (y_i - c), 1, |y_i - c|^2) (scaled coordinates, so psi =
-// 2^-(scaled distance)^2): x_i . x_j = |y_i - y_j|^2 for the chunk vectors x_j.
-// Lane half h holds slots 16 m + 8 h .. + 7 of the row pattern for the two
-// distance steps m.
-template <int NT, int NS, int RR, bool SAFE>
-__device__ __forceinline__ void setup_rows(const EParams &p, const Smem<NT, SAFE> &sm, int64_t block0, int64_t ib,
-                                           Rows<NT, NS, RR, SAFE> &rb)
+// the block of ROWS rows that starts at block0.  The loads first; rows past the
+// end read the last row and count as 0 (a branch per row would have each row's
+// load waited for in turn, some 10 us).
+template <int NT, int NS>
+struct RowLoads {
+    float y[2 * NS - 2];
+    uint32_t g[16];
+};
+
+template <int NT, int NS>
+__device__ __forceinline__ void load_rows(const EParams &p, int64_t ib, RowLoads<NT, NS> &rl)
 {
     constexpr int C = 32 * NT;
+    const int lane = threadIdx.x & 63;
+    const int h = lane >> 5;
+    const int col = lane & 31;
+    load_coords<2 * NS - 2>(p, ib + col, rl.y);
+    const uint8_t *G = p.G + ib * C + NT * col;
+    const int last = p.n - ib < 32 ? (int)(p.n - ib) - 1 : 31;      // the wave's last row (< 0: none)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int row = 8 * (r >> 2) + 4 * h + (r & 3);
+        typename Bytes<NT>::t w = 0;
+        if (last >= 0) w = *reinterpret_cast<const typename Bytes<NT>::t *>(G + (row < last ? row : last) * C);
+        rl.g[r] = w;
+    }
+}
+
+// This lane's row vector is x_i = (-2 (y_i - c), 1, |y_i - c|^2) (scaled
+// coordinates, so psi = 2^-(scaled distance)^2): x_i . x_j = |y_i - y_j|^2 for
+// the chunk vectors x_j.  Lane half h holds slots 16 m + 8 h .. + 7 of the row
+// pattern for the two distance steps m.
+template <int NT, int NS, bool SAFE>
+__device__ __forceinline__ void setup_rows(const EParams &p, const Smem<NT, SAFE> &sm, int64_t block0, int64_t ib,
+                                           const RowLoads<NT, NS> &rl, Rows<NT, NS, SAFE> &rb)
+{
     constexpr int KA = 2 * NS;
     const int lane = threadIdx.x & 63;
     const int h = lane >> 5;
     const int col = lane & 31;
     const int64_t i = ib + col;
+    const int rows = p.n - ib < 32 ? (int)(p.n - ib) : 32;      // of the wave's that exist
 #pragma unroll
-    for (int t = 0; t < NT; ++t) rb.g[t] = 0u;
-#pragma unroll
-    for (int q = 0; q < RR; ++q) rb.w[q] = 0u;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int64_t row = ib + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (row < p.n) {
-            const uint8_t *G = p.G + row * C;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) rb.g[t] |= (uint32_t)G[32 * t + col] << r;
-#pragma unroll
-            for (int q = 0; q < RR; ++q) rb.w[q] |= (q < p.R ? (uint32_t)G[q] : 0u) << r;
-        }
-    }
+    for (int r = 0; r < 16; ++r) rb.g[r] = 8 * (r >> 2) + 4 * h + (r & 3) < rows ? rl.g[r] : 0u;
     float x[KA];
     float nrm = 0.0f;
 #pragma unroll
     for (int k = 0; k < KA; ++k) x[k] = 0.0f;
 #pragma unroll
     for (int d = 0; d < KA - 2; ++d) {
-        const float y = (d < p.D && i < p.n) ? p.Y[d * p.ldY + i] : 0.0f;
-        const float v = (d < p.D && i < p.n) ? y * p.yscale - sm.cen[d] : 0.0f;
+        const bool real = d < p.D && i < p.n;
+        const float v = real ? rl.y[d] * p.yscale - sm.cen[d] : 0.0f;
         nrm = fmaf(v, v, nrm);
         if (d < p.D) x[d] = -2.0f * v;
-        if constexpr (SAFE) rb.y[d] = y;
+        if constexpr (SAFE) rb.y[d] = real ? rl.y[d] : 0.0f;
     }
     rb.far = false;
     if constexpr (SAFE) {
@@ -265,7 +311,7 @@ template <> struct Words<1> { typedef uint32_t t; };
 template <> struct Words<2> { typedef u32x2 t; };
 template <> struct Words<4> { typedef u32x4 t; };
 
-// Staging.  Columns of chunk j0 .. j0 + JC - 1 go to LDS transposed, [c][swap23(j)],
+// Staging.  Columns of chunk j0 .. j0 + JC - 1 go to LDS transposed, [32 t + col][swap23(j)],
 // as float16 (events j >= n: 0).  A thread takes 4 rows x 4 NT columns, one load of
 // 4 NT bytes per row, and writes, per column, its 4 rows as one 8-byte word.  A dword
 // of four 0/1 bytes times 60, in two 16-bit lanes, holds 0x3C for each 1, the high byte
@@ -325,9 +371,9 @@ __device__ __forceinline__ void store_columns(Smem<NT, SAFE> &sm, const u32x2 (&
 {
     const int tid = threadIdx.x;
     const int jq = swap23((tid & 31) * 4);
-    const int c0 = (tid >> 5) * 4 * NT;
+    const int c0 = (tid >> 5) * 4;       // column NT (c0 + q / NT) + q % NT
 #pragma unroll
-    for (int q = 0; q < 4 * NT; ++q) *reinterpret_cast<u32x2 *>(&sm.gs[c0 + q][jq]) = o[q];
+    for (int q = 0; q < 4 * NT; ++q) *reinterpret_cast<u32x2 *>(&sm.gs[32 * (q % NT) + c0 + q / NT][jq]) = o[q];
 }
 
 // The vectors x_j = (y_j - c, |y_j - c|^2, 1) go to LDS as [j][slot], one event per
@@ -421,8 +467,8 @@ __device__ __forceinline__ void store_events(const EParams &p, Smem<NT, SAFE> &s
 // jb + 8 (r / 4) + 4 h + r % 4, r < 16.  DIRECT (SAFE form only): as direct
 // float32 differences of the raw coordinates instead, |(y_i - y_j) yscale|^2 - 14,
 // in the same lane layout.
-template <int NT, int NS, int RR, bool SAFE, bool DIRECT>
-__device__ __forceinline__ f32x16 distances(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, RR, SAFE> &rb, int jb, int D,
+template <int NT, int NS, bool SAFE, bool DIRECT>
+__device__ __forceinline__ f32x16 distances(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, SAFE> &rb, int jb, int D,
                                             float yscale)
 {
     const int lane = threadIdx.x & 63;
@@ -488,11 +534,11 @@ __device__ __forceinline__ void psi_pair(const f32x16 &dd, int k, int jb, int re
 }
 
 // psi of a chunk's first step.
-template <int NT, int NS, int RR, bool SAFE, bool DIRECT>
-__device__ __forceinline__ void first_psi(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, RR, SAFE> &rb, Psi &cur, int D,
+template <int NT, int NS, bool SAFE, bool DIRECT>
+__device__ __forceinline__ void first_psi(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, SAFE> &rb, Psi &cur, int D,
                                           float yscale)
 {
-    const f32x16 dd = distances<NT, NS, RR, SAFE, DIRECT>(sm, b, rb, 0, D, yscale);
+    const f32x16 dd = distances<NT, NS, SAFE, DIRECT>(sm, b, rb, 0, D, yscale);
 #pragma unroll
     for (int k = 0; k < 8; ++k) psi_pair<false>(dd, k, 0, 0, cur);
 }
@@ -507,9 +553,9 @@ __device__ __forceinline__ void first_psi(const Smem<NT, SAFE> &sm, int b, const
 // pipeline runs on into the next chunk: ``cur`` enters holding psi of this
 // chunk's first step and leaves with that of the next one's, which is of use
 // when that is the row block's next chunk (SAFE: each chunk for itself).
-template <int NT, int NS, int RR, bool SAFE, bool DIRECT>
+template <int NT, int NS, bool SAFE, bool DIRECT>
 __device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, int b,
-                                               const Rows<NT, NS, RR, SAFE> &rb, f32x16 (&acc)[NT], Psi &cur, int D,
+                                               const Rows<NT, NS, SAFE> &rb, f32x16 (&acc)[NT], Psi &cur, int D,
                                                float yscale)
 {
     const int lane = threadIdx.x & 63;
@@ -527,8 +573,8 @@ __device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, int b,
     for (int st = 0; st < STEPS; ++st) {
         const bool last = st + 1 == STEPS;
         f32x16 dd = f32x16{};
-        if (!last) dd = distances<NT, NS, RR, SAFE, DIRECT>(sm, b, rb, (st + 1) * 2 * KS, D, yscale);
-        else if (!SAFE) dd = distances<NT, NS, RR, SAFE, false>(sm, b ^ 1, rb, 0, D, yscale);
+        if (!last) dd = distances<NT, NS, SAFE, DIRECT>(sm, b, rb, (st + 1) * 2 * KS, D, yscale);
+        else if (!SAFE) dd = distances<NT, NS, SAFE, false>(sm, b ^ 1, rb, 0, D, yscale);
         Psi next;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -548,8 +594,8 @@ __device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, int b,
 
 // The chunk that holds the diagonal of the wave's rows, which is its row
 // block's first: step by step, keeping psi only for j > rel.
-template <int NT, int NS, int RR, bool SAFE, bool DIRECT>
-__device__ __forceinline__ void diagonal_products(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, RR, SAFE> &rb, int rel,
+template <int NT, int NS, bool SAFE, bool DIRECT>
+__device__ __forceinline__ void diagonal_products(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, SAFE> &rb, int rel,
                                                   f32x16 (&acc)[NT], int D, float yscale)
 {
     const int lane = threadIdx.x & 63;
@@ -557,7 +603,7 @@ __device__ __forceinline__ void diagonal_products(const Smem<NT, SAFE> &sm, int 
     const int col = lane & 31;
 #pragma unroll 1
     for (int jb = 0; jb < JC; jb += 2 * KS) {
-        const f32x16 dd = distances<NT, NS, RR, SAFE, DIRECT>(sm, b, rb, jb, D, yscale);
+        const f32x16 dd = distances<NT, NS, SAFE, DIRECT>(sm, b, rb, jb, D, yscale);
         Psi psi;
 #pragma unroll
         for (int k = 0; k < 8; ++k) psi_pair<true>(dd, k, jb, rel, psi);
@@ -571,30 +617,45 @@ __device__ __forceinline__ void diagonal_products(const Smem<NT, SAFE> &sm, int 
     }
 }
 
-// Reduce the float32 tiles into the float64 partials and clear them.  Lane
-// (col, h) holds column 32 t + col for rows 8 (r / 4) + 4 h + r % 4 of its
-// wave's 32.  The leading R columns are the row weights; their values
-// (Psi_upper w_q)_i come from the lane that holds them (lane q of the half), so
-// that every column can take the transposed term sum_i G_ic (Psi_upper w_q)_i.
-template <int NT, int NS, int RR, bool SAFE>
-__device__ __forceinline__ void flush(const Rows<NT, NS, RR, SAFE> &rb, f32x16 (&acc)[NT], double (&part)[NT][1 + RR])
+// Value of lane Q < 16 of each half of the wave, in all its lanes: broadcast in
+// the rows of 16 lanes, then from the last lane of the first and third row to the
+// second and fourth (two moves on the vector ALU, no trip through LDS).
+template <int Q>
+__device__ __forceinline__ uint32_t half_lane(uint32_t x)
 {
-    const int src = threadIdx.x & 32;
+    const int t = __builtin_amdgcn_update_dpp((int)x, (int)x, 0x150 + Q, 0xf, 0xf, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(t, t, 0x142, 0xa, 0xf, false);
+}
+
+// Row weight q of row r, and (Psi_upper w_q) of it: column q of G and of the tiles.
+template <int NT, int Q>
+__device__ __forceinline__ void weight(const uint32_t (&g)[16], const f32x16 (&acc)[NT], int r, float &w, float &u)
+{
+    w = (float)((half_lane<Q / NT>(g[r]) >> (8 * (Q % NT))) & 255u);
+    const float a = acc[Q % NT][r];     // bits are taken from a scalar: of an element in place they are element 0's
+    u = __builtin_bit_cast(float, half_lane<Q / NT>(__builtin_bit_cast(uint32_t, a)));
+}
+
+// Reduce the float32 tiles into the float64 partials and clear them.  The
+// leading R columns are the row weights; their values (Psi_upper w_q)_i come
+// from the lane that holds them, so that every column can take the transposed
+// term sum_i G_ic (Psi_upper w_q)_i.
+template <int NT, int NS, int RR, bool SAFE>
+__device__ __forceinline__ void flush(const Rows<NT, NS, SAFE> &rb, f32x16 (&acc)[NT], double (&part)[NT][1 + RR])
+{
     float s0[NT], s1[NT], s2[NT], s3[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) s0[t] = s1[t] = s2[t] = s3[t] = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        float w[RR], u[RR];
-#pragma unroll
-        for (int q = 0; q < RR; ++q) {
-            w[q] = (float)((rb.w[q] >> r) & 1u);
-            u[q] = __shfl(acc[0][r], src + q);
-        }
+        float w[3], u[3];
+        weight<NT, 0>(rb.g, acc, r, w[0], u[0]);
+        if constexpr (RR > 1) weight<NT, 1>(rb.g, acc, r, w[1], u[1]);
+        if constexpr (RR > 2) weight<NT, 2>(rb.g, acc, r, w[2], u[2]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const float v = acc[t][r];
-            const float g = (float)((rb.g[t] >> r) & 1u);
+            const float g = (float)((rb.g[r] >> (8 * t)) & 255u);
             s0[t] = fmaf(g, v, s0[t]);
             s1[t] = fmaf(w[0], v, fmaf(g, u[0], s1[t]));
             if constexpr (RR > 1) s2[t] = fmaf(w[1], v, fmaf(g, u[1], s2[t]));
@@ -622,33 +683,33 @@ __device__ __forceinline__ void flush(const Rows<NT, NS, RR, SAFE> &rb, f32x16 (
 // workgroup per piece instead: at 3e4 events pieces of two chunks, 13.8 k
 // workgroups, each with its centre, its rows' columns, and 256 float64 atomics
 // on the same addresses as the others': 0.533 ms against 0.353 ms, 128 columns.)
+// All positions fit 32 bits: nb < 2^26 for any sample that fits in memory, and
+// K (nb + 1) < 2^15 + 2 nb.
 struct Seq {
-    int64_t n, nb;
-    int K;
-    __device__ __forceinline__ int64_t len1(int64_t g) const { return nb - g; }             // chunks of block g's row
-    __device__ __forceinline__ int64_t len(int64_t g) const                                  // of the pair's list
+    uint32_t nb, K;
+    __device__ __forceinline__ uint32_t len1(uint32_t g) const { return nb - g; }            // chunks of block g's row
+    __device__ __forceinline__ uint32_t len(uint32_t g) const                                 // of the pair's list
     {
         return 2 * g + 1 == nb ? nb - g : nb + 1;
     }
-    // the segment of pair g that holds list position v: its first position, end
-    __device__ __forceinline__ void segment(int64_t g, int64_t v, int64_t &s0, int64_t &s1) const
+    // the run of segments (a piece, cut at the row block's end) of pair g that
+    // holds list position v: its first position, end
+    __device__ __forceinline__ void run(uint32_t g, uint32_t v, uint32_t &a, uint32_t &b) const
     {
-        const int64_t L1 = len1(g), L = len(g);
-        const int64_t k = ((v + 1) * K - 1) / L;
-        int64_t a = k * L / K, b = (k + 1) * L / K;
+        const uint32_t L1 = len1(g), L = len(g);
+        const uint32_t k = ((v + 1) * K - 1) / L;
+        a = k * L / K;
+        b = (k + 1) * L / K;
         if (v < L1) b = b < L1 ? b : L1;
         else a = a > L1 ? a : L1;
-        s0 = a + (v - a) / FL * FL;
-        s1 = s0 + FL < b ? s0 + FL : b;
     }
-    // sequence position ``pos`` rounded down to a segment's start
-    __device__ __forceinline__ int64_t round(int64_t pos, int64_t total) const
+    // list position v of pair g, rounded down to a segment's start
+    __device__ __forceinline__ uint32_t round(uint32_t g, uint32_t v) const
     {
-        if (pos >= total) return total;
-        const int64_t g = pos / (nb + 1), v = pos % (nb + 1);
-        int64_t s0, s1;
-        segment(g, v, s0, s1);
-        return pos - (v - s0);
+        if (v >= len(g)) return v;
+        uint32_t a, b;
+        run(g, v, a, b);
+        return a + (v - a) / FL * FL;
     }
 };
 
@@ -664,10 +725,19 @@ struct Seq {
 // as a variant inside it the loop carried 70 moves and scratch reloads, and
 // the reloads waited for the loads of the next chunk).  At 3e5 events x 128
 // columns: 23.6 ms with the products unpipelined, 20.2 ms with them pipelined
-// inside a chunk, 18.8 ms in this form.
+// inside a chunk, 18.5 ms in this form.
+//
+// At 3e4 events a share is 54 chunks and the flushes count: a lane holds its
+// columns' bytes of its 16 rows (Rows), converts them one byte at a time, and
+// takes the row weights' values by lane broadcasts on the vector ALU.  With
+// the bytes reread as eight selects per row and the weights through LDS
+// permutes: 0.316 ms against 0.290 ms (128 columns), 0.203 against 0.177 ms
+// (32).  Below 1e4 a workgroup has two chunks and the time is the latency of
+// its set-up, so the loads of that are issued together: 5e3 events x 128
+// columns, 5 coordinates, 33.5 us a call with them in turn, 28.1 us so.
 template <int NT, int NS, int RR, bool SAFE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void tp_pairsum_kernel(const EParams p, const int K,
-                                                                                                 const int S, const int64_t total)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 4 || SAFE ? 2 : 3)))
+void tp_pairsum_kernel(const EParams p, const uint32_t K, const uint32_t S, const uint32_t total)
 {
     constexpr int C = 32 * NT;
     constexpr int KA = 2 * NS;
@@ -680,27 +750,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
     const int wave = tid >> 6;
     const int h = lane >> 5;
     const int col = lane & 31;
-    const Seq sq = { p.n, (p.n + ROWS - 1) / ROWS, K };
-    // this workgroup's share [pos, end) of the sequence of chunks: with S > 0 one
-    // of S parts of a pair's list (part r of every pair before part r + 1 of any,
-    // and each die given a run of this order, so that the workgroups of a die
-    // read the same chunks at about the same time), else an equal part of it all
-    int64_t pos, end;
+    const Seq sq = { (uint32_t)((p.n + ROWS - 1) / ROWS), K };
+    // this workgroup's share of the sequence of chunks, ``todo`` of them from
+    // list position v0 of pair g0 on: with S > 0 one of S parts of a pair's list
+    // (part r of every pair before part r + 1 of any, and each die given a run
+    // of this order, so that the workgroups of a die read the same chunks at
+    // about the same time), else an equal part of it all (``total`` < 2^32)
+    uint32_t g0, v0, todo;
     if (S > 0) {
-        const uint32_t pairs = (uint32_t)((sq.nb + 1) / 2), units = gridDim.x;
+        const uint32_t pairs = (sq.nb + 1) / 2, units = gridDim.x;
         const uint32_t xcd = blockIdx.x % XCDS, slot = blockIdx.x / XCDS;
         const uint32_t u = xcd * (units / XCDS) + (xcd < units % XCDS ? xcd : units % XCDS) + slot;
-        const int64_t g = u % pairs, r = u / pairs, L = sq.len(g), at = g * (sq.nb + 1);
-        pos = sq.round(at + r * L / S, total);
-        end = r + 1 < S ? sq.round(at + (r + 1) * L / S, total) : at + L;
+        const uint32_t r = u / pairs;
+        g0 = u - r * pairs;
+        const uint32_t L = sq.len(g0);
+        v0 = sq.round(g0, r * L / S);
+        todo = sq.round(g0, r + 1 < S ? (r + 1) * L / S : L) - v0;
     } else {
-        const int64_t share = total / gridDim.x, extra = total % gridDim.x, wg = blockIdx.x;
-        pos = sq.round(wg * share + (wg < extra ? wg : extra), total);
-        end = sq.round((wg + 1) * share + (wg + 1 < extra ? wg + 1 : extra), total);
+        const uint32_t share = total / gridDim.x, extra = total % gridDim.x, wg = blockIdx.x;
+        const uint32_t p0 = wg * share + (wg < extra ? wg : extra), p1 = p0 + share + (wg < extra ? 1 : 0);
+        g0 = p0 / (sq.nb + 1);
+        const uint32_t g1 = p1 / (sq.nb + 1), at0 = g0 * (sq.nb + 1), at1 = g1 * (sq.nb + 1);
+        v0 = sq.round(g0, p0 - at0);
+        todo = (p1 < total ? at1 + sq.round(g1, p1 - at1) : total) - (at0 + v0);
     }
-    const bool works = pos < end;
-    if (works) {
-        for (int e = tid; e < C * (1 + MAXR); e += 256) (&sm.red[0][0])[e] = 0.0;
+    if (todo > 0) {
+        // the loads of the set-up, all in flight together: a small sample's time is
+        // made of such latencies
+        float cy[KA - 2];
+        load_coords<KA - 2>(p, tid, cy);
         double part[NT][1 + RR];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -709,31 +787,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
         f32x16 acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = f32x16{};
-        centre(p, sm);
-        fill_slots<NT, KA, SAFE>(sm);
         // cursors of the sequence: this chunk, the next, the one after
-        struct Cursor { int64_t g, v; };
-        auto after = [&](Cursor c) { return c.v + 1 < sq.len(c.g) ? Cursor{ c.g, c.v + 1 } : Cursor{ c.g + 1, 0 }; };
+        struct Cursor { uint32_t g, v; };
+        auto after = [&](Cursor c) { return c.v + 1 < sq.len(c.g) ? Cursor{ c.g, c.v + 1 } : Cursor{ c.g + 1, 0u }; };
         // ROWS == JC: a row block starts a chunk, and its first chunk holds the diagonal
         auto chunk_j0 = [&](Cursor c) {
-            const int64_t L1 = sq.len1(c.g);
-            return (c.v < L1 ? c.g + c.v : sq.nb - 1 - c.g + (c.v - L1)) * JC;
+            const uint32_t L1 = sq.len1(c.g);
+            return (int64_t)(c.v < L1 ? c.g + c.v : sq.nb - 1 - c.g + (c.v - L1)) * JC;
         };
-        Cursor at = { pos / (sq.nb + 1), pos % (sq.nb + 1) }, at1 = after(at);
+        Cursor at = { g0, v0 }, at1 = after(at);
         Columns<NT> cols;
         Event<KA> ev;
+        Rows<NT, NS, SAFE> rb;
+        uint32_t blk;       // the row block of rb
         {
             const int64_t j0 = chunk_j0(at);
             load_columns<NT>(p, j0, cols);
             load_events<KA>(p, j0, ev);
+            RowLoads<NT, NS> rl;
+            blk = at.v < sq.len1(at.g) ? at.g : sq.nb - 1 - at.g;
+            load_rows<NT, NS>(p, (int64_t)blk * ROWS + wave * 32, rl);
+            for (int e = tid; e < C * (1 + MAXR); e += 256) (&sm.red[0][0])[e] = 0.0;
+            fill_slots<NT, KA, SAFE>(sm);
+            centre<KA - 2>(p, sm, cy);
             store_events<NT, KA, SAFE>(p, sm, 0, j0, ev);
-            if (pos + 1 < end) load_events<KA>(p, chunk_j0(at1), ev);
+            if (todo > 1) load_events<KA>(p, chunk_j0(at1), ev);
+            setup_rows<NT, NS, SAFE>(p, sm, (int64_t)blk * ROWS, (int64_t)blk * ROWS + wave * 32, rl, rb);
         }
         __syncthreads();
-        Rows<NT, NS, RR, SAFE> rb;
         Psi cur;
         bool primed = false;
-        int64_t blk = -1;
         int b = 0;
         const int rel = wave * 32 + col;
         // this chunk's columns and the next one's vectors to LDS, the loads after them issued
@@ -742,45 +825,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
             expand_columns<NT>(cols, o);
             __syncthreads();                    // the last chunk's columns have been read
             store_columns<NT, SAFE>(sm, o);
-            if (pos + 1 < end) store_events<NT, KA, SAFE>(p, sm, b ^ 1, chunk_j0(at1), ev);
+            if (todo > 1) store_events<NT, KA, SAFE>(p, sm, b ^ 1, chunk_j0(at1), ev);
             __syncthreads();
             const Cursor at2 = after(at1);
-            if (pos + 1 < end) load_columns<NT>(p, chunk_j0(at1), cols);
-            if (pos + 2 < end) load_events<KA>(p, chunk_j0(at2), ev);
+            if (todo > 1) load_columns<NT>(p, chunk_j0(at1), cols);
+            if (todo > 2) load_events<KA>(p, chunk_j0(at2), ev);
             at = at1;
             at1 = at2;
-            ++pos;
+            --todo;
         };
-        while (pos < end) {
-            const int64_t L1 = sq.len1(at.g), L = sq.len(at.g);
-            const int64_t row = at.v < L1 ? at.g : sq.nb - 1 - at.g;
-            int64_t s0, s1;
-            sq.segment(at.g, at.v, s0, s1);
-            const bool diag = at.v == 0 || at.v == L1, more = s1 != L1 && s1 != L && pos + (s1 - s0) < end;
-            int left = (int)(s1 - s0);
+        uint32_t run_end = 0;
+        while (todo > 0) {
+            const uint32_t L1 = sq.len1(at.g), L = sq.len(at.g);
+            const uint32_t row = at.v < L1 ? at.g : sq.nb - 1 - at.g;
+            if (at.v == 0 || run_end == 0 || at.v == run_end) {
+                uint32_t a;
+                sq.run(at.g, at.v, a, run_end);
+            }
+            uint32_t left = run_end - at.v < FL ? run_end - at.v : FL;      // chunks of this segment
+            const uint32_t s1 = at.v + left;
+            const bool diag = at.v == 0 || at.v == L1, more = s1 != L1 && s1 != L && left < todo;
             if (row != blk) {
-                setup_rows<NT, NS, RR, SAFE>(p, sm, row * ROWS, row * ROWS + wave * 32, rb);
+                RowLoads<NT, NS> rl;
+                load_rows<NT, NS>(p, (int64_t)row * ROWS + wave * 32, rl);
+                setup_rows<NT, NS, SAFE>(p, sm, (int64_t)row * ROWS, (int64_t)row * ROWS + wave * 32, rl, rb);
                 blk = row;
                 primed = false;
             }
             if (diag) {
                 stage();
                 if (SAFE && (rb.far || (sm.far[b][0] | sm.far[b][1]) != 0u))
-                    diagonal_products<NT, NS, RR, SAFE, SAFE>(sm, b, rb, rel, acc, p.D, p.yscale);
-                else diagonal_products<NT, NS, RR, SAFE, false>(sm, b, rb, rel, acc, p.D, p.yscale);
+                    diagonal_products<NT, NS, SAFE, SAFE>(sm, b, rb, rel, acc, p.D, p.yscale);
+                else diagonal_products<NT, NS, SAFE, false>(sm, b, rb, rel, acc, p.D, p.yscale);
                 b ^= 1;
                 --left;
             }
             if (left > 0) {
-                if (!SAFE && !primed) first_psi<NT, NS, RR, SAFE, false>(sm, b, rb, cur, p.D, p.yscale);
+                if (!SAFE && !primed) first_psi<NT, NS, SAFE, false>(sm, b, rb, cur, p.D, p.yscale);
                 do {
                     stage();
                     if (SAFE && (rb.far || (sm.far[b][0] | sm.far[b][1]) != 0u)) {
-                        first_psi<NT, NS, RR, SAFE, SAFE>(sm, b, rb, cur, p.D, p.yscale);
-                        chunk_products<NT, NS, RR, SAFE, SAFE>(sm, b, rb, acc, cur, p.D, p.yscale);
+                        first_psi<NT, NS, SAFE, SAFE>(sm, b, rb, cur, p.D, p.yscale);
+                        chunk_products<NT, NS, SAFE, SAFE>(sm, b, rb, acc, cur, p.D, p.yscale);
                     } else {
-                        if (SAFE) first_psi<NT, NS, RR, SAFE, false>(sm, b, rb, cur, p.D, p.yscale);
-                        chunk_products<NT, NS, RR, SAFE, false>(sm, b, rb, acc, cur, p.D, p.yscale);
+                        if (SAFE) first_psi<NT, NS, SAFE, false>(sm, b, rb, cur, p.D, p.yscale);
+                        chunk_products<NT, NS, SAFE, false>(sm, b, rb, acc, cur, p.D, p.yscale);
                     }
                     b ^= 1;
                 } while (--left > 0);
@@ -796,7 +885,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
             for (int q = 0; q <= RR; ++q) {
                 double x = part[t][q];
                 x += __shfl_xor(x, 32);
-                if (h == 0 && q <= R) atomicAdd(&sm.red[32 * t + col][q], x);
+                if (h == 0 && q <= R) atomicAdd(&sm.red[NT * col + t][q], x);
             }
         __syncthreads();
         for (int e = tid; e < C * (1 + R); e += 256) {
@@ -827,13 +916,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
 __global__ __launch_bounds__(256) void tp_range_kernel(const EParams p)
 {
     __shared__ CentreSmem sm;
-    centre(p, sm);
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    float cy[MAXD], y[MAXD];
+    load_coords<MAXD>(p, threadIdx.x, cy);
+    load_coords<MAXD>(p, i, y);
+    centre<MAXD>(p, sm, cy);
     if (i >= p.n) return;
     float nrm = 0.0f;
-    for (int d = 0; d < p.D; ++d) {
-        const float v = p.Y[d * p.ldY + i] * p.yscale - sm.cen[d];
-        nrm = fmaf(v, v, nrm);
+#pragma unroll
+    for (int d = 0; d < MAXD; ++d) {
+        const float v = y[d] * p.yscale - sm.cen[d];
+        nrm = d < p.D ? fmaf(v, v, nrm) : nrm;
     }
     if (!(nrm <= VMAX2)) atomicOr(p.flag, 1u);
 }
@@ -873,8 +966,10 @@ void launch_ntd(const EParams &p, hipStream_t st)
         if (grid > (total + 1) / 2) grid = (total + 1) / 2;
     }
     // one of the two instantiations works (the range check's flag), the other exits
-    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, false>), dim3((unsigned)grid), dim3(256), 0, st, p, (int)K, (int)S, total);
-    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, true>), dim3((unsigned)grid), dim3(256), 0, st, p, (int)K, (int)S, total);
+    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, false>), dim3((unsigned)grid), dim3(256), 0, st, p, (uint32_t)K,
+                       (uint32_t)S, (uint32_t)total);
+    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, true>), dim3((unsigned)grid), dim3(256), 0, st, p, (uint32_t)K,
+                       (uint32_t)S, (uint32_t)total);
 }
 
 template <int NT, int RR>
