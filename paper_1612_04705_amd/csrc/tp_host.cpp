@@ -185,6 +185,13 @@ Device &device(int id)
     return d;
 }
 
+// Whether ``st`` is being captured into a graph of the caller's.
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+}
+
 // A deferral workspace of ``cap`` list entries; its counters are cleared on ``st``.
 int new_workspace(uint64_t cap, hipStream_t st, Workspace &w)
 {
@@ -796,7 +803,7 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
     kp.mode = mode;
     kp.rep = ws.rep;
     kp.fold = p.hs.size() > 1 ? p.dfold : nullptr;
-    kp.nfold = (int32_t)p.hfold.size();
+    kp.nfold = ws.rep ? (int32_t)p.hfold.size() : 0;
     // Several scheme groups run as parallel branches (the caller's stream and
     // NSIDE side streams, in turn): their launches overlap,
     // so one kernel's last workgroups share the chip with the next kernel's
@@ -1034,6 +1041,9 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
     Workspace ws;
     rc = get_workspace(d, st, list_capacity(p->vtotal), ws);
     if (rc) return rc;
+    // a captured launch may be replayed beside this stream's own calls: it counts
+    // directly
+    if (capturing(st)) ws.rep = nullptr;
     rc = launch_plan(d, *p, gtu, prec, mode, ws, st);
     if (rc) return rc;
     return end_use(*p, st);

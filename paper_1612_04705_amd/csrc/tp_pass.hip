@@ -1077,7 +1077,7 @@ __global__ __launch_bounds__(512) void tp_pass_kernel(const KParams)
         asm volatile("" : "+s"(F));
         uint64_t *counts = F->counts;
         uint64_t *stats = F->stats;
-        if (F->rep_off >= 0) {
+        if (F->rep_off >= 0 && kf->rep) {
             uint64_t *copy = kf->rep + F->rep_off + (int64_t)((int)blockIdx.x & F->rep_mask) * rep_stride(F->nbtot);
             counts = copy;
             stats = copy + (F->nbtot + 1) * 4;

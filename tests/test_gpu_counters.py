@@ -79,3 +79,30 @@ def test_default_shapes(tp, copies):
     for call in (tp.bin, tp.bin_noalloc):
         counts, stats = call(ds, ch, bn, tp.TP_PREC_F32_RECHECK)
         assert torch.equal(counts, copies * small) and torch.equal(stats[:4], copies * st[:4])
+
+
+def test_captured_call(tp):
+    """A call captured into the caller's own graph and replayed between the stream's own calls: each adds the sample's
+    counts once."""
+    s = synth.generate(D0, 200003, 901)
+    comps, tag = s.numpy()
+    axes = [synth.absphi_axis(10)]
+    want = oracle.run(comps, tag, D0.triple, D0.planes, axes)
+    ds, bn, ch = tp.DeviceSample.from_sample(s), tp.Binning(axes), tp.channel(D0.triple, D0.planes)
+    counts, stats = tp.new_counts(bn)
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(st):
+        for _ in range(2):                          # its plan and workspace are made outside the capture
+            tp.bin(ds, ch, bn, tp.TP_PREC_F32_RECHECK, counts, stats)
+        st.synchronize()
+        with torch.cuda.graph(g, stream=st, capture_error_mode="thread_local"):
+            tp.bin(ds, ch, bn, tp.TP_PREC_F32_RECHECK, counts, stats, check=False)
+        calls = 2
+        for _ in range(4):
+            g.replay()
+            tp.bin(ds, ch, bn, tp.TP_PREC_F32_RECHECK, counts, stats)
+            calls += 2
+            assert table(bn, counts) == [[calls * v for v in row] for row in want["counts"]]
+            assert [int(v) for v in stats[:4].cpu()] == [calls * v for v in want["stats"]]
