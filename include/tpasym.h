@@ -180,6 +180,15 @@ int tp_bin(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int3
            uint64_t *counts, tp_stats *stats, void *stream);
 
 /*
+ * tp_bin_checked -- tp_bin, then a wait for the stream's work.
+ *   unresolved: host; stats->n_unresolved after the call (what earlier calls
+ *               added included).  The last kernel stores it in host memory, so
+ *               no copy follows the wait.  Not under graph capture.
+ */
+int tp_bin_checked(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int32_t precision,
+                   uint64_t *counts, tp_stats *stats, void *stream, uint64_t *unresolved);
+
+/*
  * tp_bin_noalloc -- tp_bin for callers that cannot allocate device memory
  * (code under HIP graph capture, fixed-memory serving loops): the same
  * arguments, outputs and results, but the launch tables, the exact tier's

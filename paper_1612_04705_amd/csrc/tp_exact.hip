@@ -311,6 +311,10 @@ __global__ __launch_bounds__(64) void tp_exact_kernel(const KParams kp)
     if (last && threadIdx.x == 0) {
         *kp.xcount = 0u;
         *kp.xdone = 0u;
+        if (kp.mail) {
+            const uint64_t u = __hip_atomic_load(kp.samples[0].stats + ST_UNRESOLVED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(kp.mail, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
         __threadfence();
     }
 }

@@ -172,6 +172,35 @@ constexpr int LARGEST_WG_PER_CU = 16;
 
 std::mutex g_mu;
 std::map<int, Device> g_dev;
+
+// Host words that a launch's last kernel stores a count in, one page of them for
+// the process, a cache line each: taken by a call and given back once the launch
+// has ended.  All calls beyond MAILS at a time read the count by a copy.
+constexpr int MAILS = 32;
+constexpr int MAIL_WORDS = 16;
+uint64_t *g_mail = nullptr;
+std::vector<int> g_mail_free;
+
+// A free word (under g_mu), or null.
+uint64_t *take_mail()
+{
+    if (!g_mail) {
+        void *m = nullptr;
+        if (hipHostMalloc(&m, MAILS * MAIL_WORDS * sizeof(uint64_t), hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        g_mail = static_cast<uint64_t *>(m);
+        for (int i = 0; i < MAILS; ++i) g_mail_free.push_back(i);
+    }
+    if (g_mail_free.empty()) return nullptr;
+    const int i = g_mail_free.back();
+    g_mail_free.pop_back();
+    return g_mail + i * MAIL_WORDS;
+}
+
+void give_mail(uint64_t *m) { g_mail_free.push_back((int)((m - g_mail) / MAIL_WORDS)); }
+
 TimingState g_timing;
 
 Device &device(int id)
@@ -781,7 +810,7 @@ int launch_group(int cus, const Group &g, tp_tuning tu, int dtype, int prec, int
 // launch shape gtu[g]; only the group ``only`` when it is >= 0), then the
 // exact tier over the shared deferral list.
 int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int prec, int mode,
-                const Workspace &ws, hipStream_t st, int only = -1)
+                const Workspace &ws, hipStream_t st, int only = -1, uint64_t *mail = nullptr)
 {
     if (p.vtotal == 0) return TP_OK;
     const bool timed = g_timing.on && !g_timing.ring.empty();
@@ -804,6 +833,7 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
     kp.rep = ws.rep;
     kp.fold = p.hs.size() > 1 ? p.dfold : nullptr;
     kp.nfold = ws.rep ? (int32_t)p.hfold.size() : 0;
+    kp.mail = mail;
     // Several scheme groups run as parallel branches (the caller's stream and
     // NSIDE side streams, in turn): their launches overlap,
     // so one kernel's last workgroups share the chip with the next kernel's
@@ -963,13 +993,14 @@ std::vector<tp_tuning> resolve_tunings(Device &d, const Plan &p, const std::vect
     std::vector<tp_tuning> out(p.groups.size());
     tp_tuning whole;
     std::memset(&whole, 0, sizeof whole);
-    if (!tuning) {
+    const bool tuned = !tuning && !d.tuned.empty();
+    if (tuned) {
         auto it = d.tuned.find(tune_key(rq, prec));
         if (it != d.tuned.end()) whole = it->second;
     }
     for (size_t g = 0; g < p.groups.size(); ++g) {
         tp_tuning t = tuning ? *tuning : whole;
-        if (!tuning) {
+        if (tuned) {
             auto it = d.tuned.find(group_key(p, p.groups[g], prec));
             if (it != d.tuned.end()) t = it->second;
         }
@@ -985,7 +1016,10 @@ int current_device(int &id)
     return TP_OK;
 }
 
-int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning, int flags, hipStream_t st)
+// ``mail`` (one request only): gets a host word that holds stats->n_unresolved
+// once the launch has ended, or null.
+int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning, int flags, hipStream_t st,
+        uint64_t **mail = nullptr)
 {
     int dev = 0;
     int rc = current_device(dev);
@@ -1044,7 +1078,8 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
     // a captured launch may be replayed beside this stream's own calls: it counts
     // directly
     if (capturing(st)) ws.rep = nullptr;
-    rc = launch_plan(d, *p, gtu, prec, mode, ws, st);
+    if (mail) *mail = take_mail();
+    rc = launch_plan(d, *p, gtu, prec, mode, ws, st, -1, mail ? *mail : nullptr);
     if (rc) return rc;
     return end_use(*p, st);
 }
@@ -1136,8 +1171,10 @@ int tp_compute(const tp_events *ev, const tp_channel *ch, int32_t precision, int
     return run(rq, precision, 1, nullptr, 0, static_cast<hipStream_t>(stream));
 }
 
-int tp_bin(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int32_t precision, uint64_t *counts,
-           tp_stats *stats, void *stream)
+namespace {
+
+int bin_one(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int32_t precision, uint64_t *counts,
+            tp_stats *stats, void *stream, uint64_t **mail)
 {
     int rc = check_events(ev, precision);
     if (rc) return rc;
@@ -1150,7 +1187,37 @@ int tp_bin(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int3
     if (!counts || !stats) return fail(TP_EINVAL, "counts and stats are required");
     if (ev->n == 0) return TP_OK;
     std::vector<Req> rq{ Req{ ev, ch, bn, counts, stats, nullptr, nullptr } };
-    return run(rq, precision, 0, nullptr, 0, static_cast<hipStream_t>(stream));
+    return run(rq, precision, 0, nullptr, 0, static_cast<hipStream_t>(stream), mail);
+}
+
+}  // namespace
+
+int tp_bin(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int32_t precision, uint64_t *counts,
+           tp_stats *stats, void *stream)
+{
+    return bin_one(ev, ch, bn, precision, counts, stats, stream, nullptr);
+}
+
+// The count comes through a host word that the launch's last kernel writes: a
+// copy of it after the wait, with its own wait, costs some 13 us, a third of a
+// call of 1e3 events.
+int tp_bin_checked(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int32_t precision,
+                   uint64_t *counts, tp_stats *stats, void *stream, uint64_t *unresolved)
+{
+    if (!unresolved) return fail(TP_EINVAL, "unresolved is required");
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    uint64_t *mail = nullptr;
+    const int rc = bin_one(ev, ch, bn, precision, counts, stats, stream, &mail);
+    if (rc) return rc;      // a word taken by a launch that failed is not used again
+    TP_HIP(hipStreamSynchronize(st));
+    if (!mail) {
+        TP_HIP(hipMemcpy(unresolved, &stats->n_unresolved, sizeof *unresolved, hipMemcpyDeviceToHost));
+        return TP_OK;
+    }
+    *unresolved = *static_cast<volatile uint64_t *>(mail);
+    std::lock_guard<std::mutex> lk(g_mu);
+    give_mail(mail);
+    return TP_OK;
 }
 
 int tp_bin_noalloc(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int32_t precision,
@@ -1533,6 +1600,11 @@ int tp_release(void)
         if (d.fork) hipEventDestroy(d.fork);
     }
     g_dev.clear();
+    if ((int)g_mail_free.size() == MAILS) {     // no call is still reading its word
+        hipHostFree(g_mail);
+        g_mail = nullptr;
+        g_mail_free.clear();
+    }
     return TP_OK;
 }
 

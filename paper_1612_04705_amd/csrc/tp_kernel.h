@@ -77,6 +77,7 @@ struct KParams {
     uint64_t *rep;            // replica array (zero between launches)
     const uint32_t *fold;     // work items of the fold: sample << 8 | item of the sample (null: one sample)
     int32_t nfold;
+    uint64_t *mail;           // host memory the last exact-tier workgroup writes sample 0's n_unresolved to (null: none)
 };
 
 // Edge data layout per axis (at eoff):

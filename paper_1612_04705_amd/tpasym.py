@@ -7,6 +7,7 @@ there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 from dataclasses import dataclass
 
@@ -86,6 +87,8 @@ def load():
                        ctypes.c_void_p, ctypes.c_void_p],
         "tp_bin": [P(_Events), P(_Channel), P(_Binning), ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
                    ctypes.c_void_p],
+        "tp_bin_checked": [P(_Events), P(_Channel), P(_Binning), ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
+                           ctypes.c_void_p, P(ctypes.c_uint64)],
         "tp_asym": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p],
         "tp_scp": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, P(ctypes.c_double),
                    P(ctypes.c_int64), P(ctypes.c_double)],
@@ -121,8 +124,8 @@ def load():
 
 
 def exported_symbols():
-    return ("tp_compute", "tp_bin", "tp_bin_noalloc", "tp_probe_f32", "tp_asym", "tp_scp", "tp_batch", "tp_autotune", "tp_timing_enable",
-            "tp_timing_reset", "tp_timing_read", "tp_release", "tp_strerror", "tp_version", "tp_coords",
+    return ("tp_compute", "tp_bin", "tp_bin_checked", "tp_bin_noalloc", "tp_probe_f32", "tp_asym", "tp_scp", "tp_batch",
+            "tp_autotune", "tp_timing_enable", "tp_timing_reset", "tp_timing_read", "tp_release", "tp_strerror", "tp_version", "tp_coords",
             "tp_pairsums", "tp_energy_eq2", "tp_energy_eq3")
 
 
@@ -163,15 +166,16 @@ class DeviceSample:
 
     def events(self) -> _Events:
         e = _Events()
-        e.n = self.n
+        n = e.n = self.n
         dt = self.comps[0].dtype
-        if dt not in (torch.float32, torch.float64) or any(t.dtype != dt for t in self.comps):
+        if dt not in (torch.float32, torch.float64) or any([t.dtype != dt for t in self.comps]):
             raise TPError("components must all be float32 or all float64")
         e.dtype = TP_F32 if dt == torch.float32 else TP_F64
+        p = e.p
         for k, t in enumerate(self.comps):
-            if not t.is_contiguous() or t.numel() != self.n:
+            if not t.is_contiguous() or t.numel() != n:
                 raise TPError("component tensors must be contiguous with n elements")
-            e.p[k] = t.data_ptr()
+            p[k] = t.data_ptr()
         if self.tag.dtype != torch.int8:
             raise TPError("tag must be int8")
         _on_one_gpu(self.tag, *self.comps)
@@ -211,13 +215,14 @@ class Binning:
 
     @property
     def nrows(self):
-        return int(np.prod(self.nbins)) + 1 if self.nbins else 1
+        return math.prod(self.nbins) + 1 if self.nbins else 1
 
 
 def new_counts(binning: Binning, device="cuda"):
-    """Zeroed device counters: counts int64[(nbins+1)*4] (read as uint64) and stats int64[8]."""
-    return (torch.zeros(binning.nrows * 4, dtype=torch.int64, device=device),
-            torch.zeros(8, dtype=torch.int64, device=device))
+    """Zeroed device counters: counts int64[(nbins+1)*4] (read as uint64) and stats int64[8],
+    views of one allocation (one fill kernel instead of two)."""
+    both = torch.zeros(binning.nrows * 4 + 8, dtype=torch.int64, device=device)
+    return both[:-8], both[-8:]
 
 
 def _check_counts(bn: Binning, counts, stats, ds: DeviceSample):
@@ -232,8 +237,12 @@ def raise_if_unresolved(stats, stream=None):
     """Synchronise ``stream`` and raise if the statistics ``stats`` (device int64 [8]) count
     events no tier could decide (components spanning more binary orders of magnitude than
     the exact tier holds): their classes are then missing from the counts."""
-    (stream or torch.cuda.current_stream(stats.device)).synchronize()
-    n = int(stats[6].item())
+    if stream and stream != torch.cuda.current_stream(stats.device):    # the current stream: item() waits for it
+        stream.synchronize()
+    _raise_unresolved(int(stats[6].item()))
+
+
+def _raise_unresolved(n):
     if n:
         raise TPError(f"{n} event(s) unresolved: components span beyond the exact tier's exponent range")
 
@@ -269,8 +278,14 @@ def bin(ds: DeviceSample, ch: _Channel, bn: Binning, precision=TP_PREC_F64, coun
     if counts is None or stats is None:
         counts, stats = new_counts(bn, ds.tag.device)
     _check_counts(bn, counts, stats, ds)
-    _check(lib.tp_bin(ctypes.byref(ev), ctypes.byref(ch), ctypes.byref(bn.b), int(precision),
-                      ctypes.c_void_p(counts.data_ptr()), ctypes.c_void_p(stats.data_ptr()), _stream(stream)))
+    args = (ctypes.byref(ev), ctypes.byref(ch), ctypes.byref(bn.b), int(precision),
+            ctypes.c_void_p(counts.data_ptr()), ctypes.c_void_p(stats.data_ptr()), _stream(stream))
+    if check and ev.n and (stream is None or hasattr(stream, "cuda_stream")):
+        n = ctypes.c_uint64()
+        _check(lib.tp_bin_checked(*args, ctypes.byref(n)))
+        _raise_unresolved(n.value)
+        return counts, stats
+    _check(lib.tp_bin(*args))
     if check:
         raise_if_unresolved(stats, stream)
     return counts, stats
