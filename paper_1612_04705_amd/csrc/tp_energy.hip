@@ -476,16 +476,18 @@ __device__ __forceinline__ f32x16 distances(const Smem<NT, SAFE> &sm, int b, con
     const int col = lane & 31;
     f32x16 dd = f32x16{};
     if constexpr (DIRECT) {
+        // No branch per row, which would have each row's reads waited for in turn
+        // (5e4 events x 32 columns, 3 coordinates, all out of range: 733 against
+        // 680 us): a coordinate beyond D is 0 on both sides and adds (0 x 0)^2.
+        const float last = D == 2 * NS - 2 ? yscale : 0.0f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int j = jb + 8 * (r >> 2) + 4 * h + (r & 3);
             float d2 = 0.0f;
 #pragma unroll
             for (int d = 0; d < 2 * NS - 2; ++d) {
-                if (d < 2 * NS - 3 || d < D) {
-                    const float t = (rb.y[d] - sm.yc[b][j][d]) * yscale;
-                    d2 = fmaf(t, t, d2);
-                }
+                const float t = (rb.y[d] - sm.yc[b][j][d]) * (d < 2 * NS - 3 ? yscale : last);
+                d2 = fmaf(t, t, d2);
             }
             dd[r] = d2 - PSI_LOG2;
         }
@@ -736,7 +738,7 @@ struct Seq {
 // its set-up, so the loads of that are issued together: 5e3 events x 128
 // columns, 5 coordinates, 33.5 us a call with them in turn, 28.1 us so.
 template <int NT, int NS, int RR, bool SAFE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 4 || SAFE ? 2 : 3)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 4 ? 2 : 3)))
 void tp_pairsum_kernel(const EParams p, const uint32_t K, const uint32_t S, const uint32_t total)
 {
     constexpr int C = 32 * NT;
@@ -962,7 +964,14 @@ void launch_ntd(const EParams &p, hipStream_t st)
         }
         grid = pairs * S;
     } else {
-        grid = grid < RESIDENT ? RESIDENT : grid > 16 * RESIDENT ? 16 * RESIDENT : grid / RESIDENT * RESIDENT;
+        // With 32 or 64 columns three workgroups fit a compute unit.  From 6
+        // chunks a share on all three are used: 4e4 events x 32 columns 273 us
+        // with two, 240 with three; x 64 330 and 303; 12345 x 64 52 and 49; at
+        // 9000 (3 chunks a share) 38 and 41.  (Out-of-range samples: 5e4 x 32
+        // 899 and 721, 3e4 x 64 432 and 407, though at three the direct
+        // distances spill.)
+        const int64_t resident = NT < 4 && total >= 6 * (RESIDENT + RESIDENT / 2) ? RESIDENT + RESIDENT / 2 : RESIDENT;
+        grid = grid < resident ? resident : grid > 16 * resident ? 16 * resident : grid / resident * resident;
         if (grid > (total + 1) / 2) grid = (total + 1) / 2;
     }
     // one of the two instantiations works (the range check's flag), the other exits

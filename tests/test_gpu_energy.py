@@ -527,3 +527,23 @@ def test_pairsums_work_split(tp, n, C, R):
     M = energy.column_pair_sums(Y.cpu().numpy(), cols, 0.3)
     want = np.stack([np.diag(M)] + [M[q] for q in range(R)], axis=1)
     assert np.all(np.abs(sums.cpu().numpy() - want) <= 1e-5 * np.abs(want))
+
+
+@pytest.mark.parametrize("n,C,R,far", [(12160, 32, 1, False), (12161, 32, 2, False), (12161, 64, 1, True), (12289, 32, 3, True)])
+def test_pairsums_shares_of_three_workgroups(tp, n, C, R, far):
+    """Around 95 and 96 row blocks, where samples of 32 and 64 columns begin to be split for three workgroups per
+    compute unit, with every distance in the matrix-core range and with far events in each 64th place.  Odd and
+    even coordinate counts (the last operand slot unused or used).  Against dense float64 sums on the same float32
+    coordinates; the library promises 1e-5."""
+    ch, s = sample(n, 400 + n)
+    Y = tp.coords(tp.DeviceSample.from_sample(s), MASKS[:5 - n % 2], 1e-3)
+    if far:
+        Y[:, 63::64] += 20.0
+    rng = np.random.default_rng(n)
+    cols = (rng.uniform(size=(n, C)) < 0.5).astype(np.uint8)
+    cols[0, :] = cols[n - 1, :] = 1
+    sums = tp.pairsums(Y, torch.from_numpy(cols).cuda(), 0.3, nrow=R)
+    torch.cuda.synchronize()
+    M = energy.column_pair_sums(Y.cpu().numpy(), cols, 0.3)
+    want = np.stack([np.diag(M)] + [M[q] for q in range(R)], axis=1)
+    assert np.all(np.abs(sums.cpu().numpy() - want) <= 1e-5 * np.abs(want))
