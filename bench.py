@@ -180,8 +180,9 @@ def energy_leg(n, nperm, dev, per_pass=126, cpu_events=0):
     T_obs = T_obs_passes[0]
     T_perm = np.array(T_perm)
     # psi is symmetric: the kernel forms each unordered pair once per launch.  Per
-    # pair and launch it spends two units, which on gfx950 do not overlap
-    # (measured), so its bound is the sum of their minimum times:
+    # pair and launch it spends two units; the reported bound is the sum of their
+    # minimum times (they overlap in part, so the fraction can pass 1 in principle;
+    # the matrix cores' share alone is the larger of the two):
     #   float16 matrix cores: the distances x_i . x_j as one contraction over
     #     32 float16 slots (split terms), 64 flops; the contraction with the C
     #     columns as two float16 terms, 4 C flops;
