@@ -91,7 +91,7 @@ struct Smem {
     double red[C][1 + MAXR];            // workgroup totals
     // SAFE: raw coordinates of the two chunks (direct distances), and whether an event of
     // the first / second 64 of each is outside the matrix-core range
-    float yc[2][SAFE ? JC : 1][MAXD];
+    alignas(16) float yc[2][SAFE ? MAXD : 1][SAFE ? JC : 1];
     uint32_t far[2][2];
 };
 
@@ -432,7 +432,7 @@ __device__ __forceinline__ void store_events(const EParams &p, Smem<NT, SAFE> &s
         const float v = (d < KA - 3 || all) && real ? pd.y[d] * p.yscale - sm.cen[d] : 0.0f;
         nrm = fmaf(v, v, nrm);
         x[d] = v;
-        if constexpr (SAFE) sm.yc[b][tid][d] = real ? pd.y[d] : 0.0f;
+        if constexpr (SAFE) sm.yc[b][d][tid] = real ? pd.y[d] : 0.0f;
     }
     if constexpr (SAFE) {
         const bool far = !(nrm <= VMAX2);
@@ -476,21 +476,27 @@ __device__ __forceinline__ f32x16 distances(const Smem<NT, SAFE> &sm, int b, con
     const int col = lane & 31;
     f32x16 dd = f32x16{};
     if constexpr (DIRECT) {
-        // No branch per row, which would have each row's reads waited for in turn
-        // (5e4 events x 32 columns, 3 coordinates, all out of range: 733 against
-        // 680 us): a coordinate beyond D is 0 on both sides and adds (0 x 0)^2.
-        const float last = D == 2 * NS - 2 ? yscale : 0.0f;
+        // Coordinate by coordinate, so that a read gives it for 4 rows and only 16
+        // values are held beside the sums (read row by row, the rows' coordinates
+        // filled the registers).  No branch: a coordinate beyond D is 0 on both
+        // sides and adds (0 x 0)^2; with one per row, each row's reads were waited
+        // for in turn (5e4 events x 32 columns, 3 coordinates, all out of range: 733
+        // against 680 us).
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int j = jb + 8 * (r >> 2) + 4 * h + (r & 3);
-            float d2 = 0.0f;
+        for (int d = 0; d < 2 * NS - 2; ++d) {
+            const float scale = d < 2 * NS - 3 || D == 2 * NS - 2 ? yscale : 0.0f;
 #pragma unroll
-            for (int d = 0; d < 2 * NS - 2; ++d) {
-                const float t = (rb.y[d] - sm.yc[b][j][d]) * (d < 2 * NS - 3 ? yscale : last);
-                d2 = fmaf(t, t, d2);
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 y = *reinterpret_cast<const f32x4 *>(&sm.yc[b][d][jb + 8 * g + 4 * h]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float t = (rb.y[d] - y[e]) * scale;
+                    dd[4 * g + e] = fmaf(t, t, dd[4 * g + e]);
+                }
             }
-            dd[r] = d2 - PSI_LOG2;
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dd[r] -= PSI_LOG2;
     } else {
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
@@ -536,11 +542,10 @@ __device__ __forceinline__ void psi_pair(const f32x16 &dd, int k, int jb, int re
 }
 
 // psi of a chunk's first step.
-template <int NT, int NS, bool SAFE, bool DIRECT>
-__device__ __forceinline__ void first_psi(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, SAFE> &rb, Psi &cur, int D,
-                                          float yscale)
+template <int NT, int NS>
+__device__ __forceinline__ void first_psi(const Smem<NT, false> &sm, int b, const Rows<NT, NS, false> &rb, Psi &cur)
 {
-    const f32x16 dd = distances<NT, NS, SAFE, DIRECT>(sm, b, rb, 0, D, yscale);
+    const f32x16 dd = distances<NT, NS, false, false>(sm, b, rb, 0, 0, 0.0f);
 #pragma unroll
     for (int k = 0; k < 8; ++k) psi_pair<false>(dd, k, 0, 0, cur);
 }
@@ -554,11 +559,14 @@ __device__ __forceinline__ void first_psi(const Smem<NT, SAFE> &sm, int b, const
 // the fences keep the interleaving, which the scheduler would undo.  The
 // pipeline runs on into the next chunk: ``cur`` enters holding psi of this
 // chunk's first step and leaves with that of the next one's, which is of use
-// when that is the row block's next chunk (SAFE: each chunk for itself).
-template <int NT, int NS, bool SAFE, bool DIRECT>
-__device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, int b,
-                                               const Rows<NT, NS, SAFE> &rb, f32x16 (&acc)[NT], Psi &cur, int D,
-                                               float yscale)
+// when that is the row block's next chunk.  The SAFE form goes step by step
+// instead (step_products): its time is the direct distances on the vector ALU,
+// and with their coordinates the pipelined form spilled 50 to 110 registers (9e3
+// events x 64 columns, 8 coordinates, out of range: 112 us with it, 97 us
+// without; 2e4 x 128, 4 coordinates: 239 and 225 us).
+template <int NT, int NS>
+__device__ __forceinline__ void chunk_products(const Smem<NT, false> &sm, int b, const Rows<NT, NS, false> &rb,
+                                               f32x16 (&acc)[NT], Psi &cur)
 {
     const int lane = threadIdx.x & 63;
     const int h = lane >> 5;
@@ -574,9 +582,8 @@ __device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, int b,
 #pragma unroll
     for (int st = 0; st < STEPS; ++st) {
         const bool last = st + 1 == STEPS;
-        f32x16 dd = f32x16{};
-        if (!last) dd = distances<NT, NS, SAFE, DIRECT>(sm, b, rb, (st + 1) * 2 * KS, D, yscale);
-        else if (!SAFE) dd = distances<NT, NS, SAFE, false>(sm, b ^ 1, rb, 0, D, yscale);
+        const f32x16 dd = last ? distances<NT, NS, false, false>(sm, b ^ 1, rb, 0, 0, 0.0f)
+                               : distances<NT, NS, false, false>(sm, b, rb, (st + 1) * 2 * KS, 0, 0.0f);
         Psi next;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -587,18 +594,19 @@ __device__ __forceinline__ void chunk_products(const Smem<NT, SAFE> &sm, int b,
             acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, cur.lo[m]), B, acc[t], 0, 0, 0);
 #pragma unroll
             for (int k = 8 * q / Q; k < 8 * (q + 1) / Q; ++k)
-                if (!last || !SAFE) psi_pair<false>(dd, k, 0, 0, next);
+                psi_pair<false>(dd, k, 0, 0, next);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (!last || !SAFE) cur = next;
+        cur = next;
     }
 }
 
-// The chunk that holds the diagonal of the wave's rows, which is its row
-// block's first: step by step, keeping psi only for j > rel.
-template <int NT, int NS, bool SAFE, bool DIRECT>
-__device__ __forceinline__ void diagonal_products(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, SAFE> &rb, int rel,
-                                                  f32x16 (&acc)[NT], int D, float yscale)
+// A chunk step by step: the one that holds the diagonal of the wave's rows
+// (MASK: psi only for j > rel), which is its row block's first, and every chunk
+// of the SAFE form.
+template <int NT, int NS, bool SAFE, bool DIRECT, bool MASK>
+__device__ __forceinline__ void step_products(const Smem<NT, SAFE> &sm, int b, const Rows<NT, NS, SAFE> &rb, int rel,
+                                              f32x16 (&acc)[NT], int D, float yscale)
 {
     const int lane = threadIdx.x & 63;
     const int h = lane >> 5;
@@ -608,7 +616,7 @@ __device__ __forceinline__ void diagonal_products(const Smem<NT, SAFE> &sm, int 
         const f32x16 dd = distances<NT, NS, SAFE, DIRECT>(sm, b, rb, jb, D, yscale);
         Psi psi;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) psi_pair<true>(dd, k, jb, rel, psi);
+        for (int k = 0; k < 8; ++k) psi_pair<MASK>(dd, k, jb, rel, psi);
 #pragma unroll
         for (int q = 0; q < 2 * NT; ++q) {
             const int m = q / NT, t = q % NT;
@@ -857,22 +865,20 @@ void tp_pairsum_kernel(const EParams p, const uint32_t K, const uint32_t S, cons
             if (diag) {
                 stage();
                 if (SAFE && (rb.far || (sm.far[b][0] | sm.far[b][1]) != 0u))
-                    diagonal_products<NT, NS, SAFE, SAFE>(sm, b, rb, rel, acc, p.D, p.yscale);
-                else diagonal_products<NT, NS, SAFE, false>(sm, b, rb, rel, acc, p.D, p.yscale);
+                    step_products<NT, NS, SAFE, SAFE, true>(sm, b, rb, rel, acc, p.D, p.yscale);
+                else step_products<NT, NS, SAFE, false, true>(sm, b, rb, rel, acc, p.D, p.yscale);
                 b ^= 1;
                 --left;
             }
             if (left > 0) {
-                if (!SAFE && !primed) first_psi<NT, NS, SAFE, false>(sm, b, rb, cur, p.D, p.yscale);
+                if constexpr (!SAFE)
+                    if (!primed) first_psi<NT, NS>(sm, b, rb, cur);
                 do {
                     stage();
-                    if (SAFE && (rb.far || (sm.far[b][0] | sm.far[b][1]) != 0u)) {
-                        first_psi<NT, NS, SAFE, SAFE>(sm, b, rb, cur, p.D, p.yscale);
-                        chunk_products<NT, NS, SAFE, SAFE>(sm, b, rb, acc, cur, p.D, p.yscale);
-                    } else {
-                        if (SAFE) first_psi<NT, NS, SAFE, false>(sm, b, rb, cur, p.D, p.yscale);
-                        chunk_products<NT, NS, SAFE, false>(sm, b, rb, acc, cur, p.D, p.yscale);
-                    }
+                    if constexpr (!SAFE) chunk_products<NT, NS>(sm, b, rb, acc, cur);
+                    else if (rb.far || (sm.far[b][0] | sm.far[b][1]) != 0u)
+                        step_products<NT, NS, SAFE, true, false>(sm, b, rb, rel, acc, p.D, p.yscale);
+                    else step_products<NT, NS, SAFE, false, false>(sm, b, rb, rel, acc, p.D, p.yscale);
                     b ^= 1;
                 } while (--left > 0);
                 primed = more;
@@ -968,8 +974,7 @@ void launch_ntd(const EParams &p, hipStream_t st)
         // chunks a share on all three are used: 4e4 events x 32 columns 273 us
         // with two, 240 with three; x 64 330 and 303; 12345 x 64 52 and 49; at
         // 9000 (3 chunks a share) 38 and 41.  (Out-of-range samples: 5e4 x 32
-        // 899 and 721, 3e4 x 64 432 and 407, though at three the direct
-        // distances spill.)
+        // 899 and 721, 3e4 x 64 432 and 407.)
         const int64_t resident = NT < 4 && total >= 6 * (RESIDENT + RESIDENT / 2) ? RESIDENT + RESIDENT / 2 : RESIDENT;
         grid = grid < resident ? resident : grid > 16 * resident ? 16 * resident : grid / resident * resident;
         if (grid > (total + 1) / 2) grid = (total + 1) / 2;
