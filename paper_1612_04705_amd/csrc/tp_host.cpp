@@ -732,12 +732,18 @@ int build_plan(Device &d, const std::vector<Req> &rq, int mode, hipStream_t st, 
 // bins: 4108), fewer and larger ranges: 2, 8 and 16 with the upper bound at 4e7
 // (1e6 events: 25.5 us with 2, 36.5 with 4; 3e7: 338 us with 8, 346 with 16),
 // and one LDS copy instead of one per wave (1e6: 25.5 against 27.1 us).
-void defaults(tp_tuning &t, int64_t nv, int stride)
+// float64 storage: 4 up to 2e7 and 8 beyond.  An event is twice the bytes, so
+// ranges are long enough at 4, and at 8 and 1.6e7 to 1.7e7 events, where a range
+// is about 2^13 events, the launch takes 7 to 14 % longer (1.6e7 |Phi|: 331 us
+// with 4, 355 with 8; 32 x 32 mass bins: 329 and 374; 2.7e7: 549 and 537, 549 and
+// 546).
+void defaults(tp_tuning &t, int64_t nv, int stride, int dtype)
 {
     const bool wide = stride > 1024;
     if (t.block != 256 && t.block != 512) t.block = 256;
     if (t.wg_per_cu < 1 || t.wg_per_cu > 32)
-        t.wg_per_cu = nv < 4000000 ? (wide ? 2 : 4) : nv < (wide ? 40000000 : 20000000) ? 8 : 16;
+        t.wg_per_cu = nv < 4000000 ? (wide ? 2 : 4)
+                    : dtype == TP_F64 ? (nv < 20000000 ? 4 : 8) : nv < (wide ? 40000000 : 20000000) ? 8 : 16;
     const int waves = t.block / 64;
     if (t.lds_copies < 1 || t.lds_copies > waves) t.lds_copies = wide ? 1 : waves;
     if (t.unroll != 1 && t.unroll != 2 && t.unroll != 4) t.unroll = 1;
@@ -773,7 +779,7 @@ int side_streams(Device &d)
 int launch_group(int cus, const Group &g, tp_tuning tu, int dtype, int prec, int mode, KParams kp, hipStream_t st)
 {
     const int64_t nv = g.vend - g.vbeg;
-    defaults(tu, nv, g.hist_stride);
+    defaults(tu, nv, g.hist_stride, dtype);
     const int epl = dtype == TP_F32 ? tu.unroll : std::min(tu.unroll, 2);
     const int64_t tile = (int64_t)epl * tu.block;
     int copies = tu.lds_copies;
@@ -1004,7 +1010,7 @@ std::vector<tp_tuning> resolve_tunings(Device &d, const Plan &p, const std::vect
             auto it = d.tuned.find(group_key(p, p.groups[g], prec));
             if (it != d.tuned.end()) t = it->second;
         }
-        defaults(t, p.groups[g].vend - p.groups[g].vbeg, p.groups[g].hist_stride);
+        defaults(t, p.groups[g].vend - p.groups[g].vbeg, p.groups[g].hist_stride, p.dtype);
         out[g] = t;
     }
     return out;
@@ -1344,7 +1350,7 @@ int tp_autotune(const tp_sample *samples, int32_t nsamples, int32_t precision, v
     }
     if (!any_events) {   // nothing to time: the default shape
         tp_tuning t{};
-        defaults(t, 0, 0);
+        defaults(t, 0, 0, TP_F32);
         *best = t;
         return TP_OK;
     }
