@@ -53,10 +53,12 @@
 #include <stdint.h>
 
 #include "tp_energy.h"
+#include "tp_launch.h"
 #define TP_HD __host__ __device__
 #include "tp_exact.h"
 
 namespace tpe {
+using tpk::launch;
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -940,7 +942,7 @@ __global__ __launch_bounds__(256) void tp_range_kernel(const EParams p)
 }
 
 template <int NT, int NS, int RR>
-void launch_ntd(const EParams &p, hipStream_t st)
+hipError_t launch_ntd(const EParams &p, hipStream_t st)
 {
     const int64_t nb = (p.n + ROWS - 1) / ROWS;
     const int64_t pairs = (nb + 1) / 2;
@@ -980,29 +982,30 @@ void launch_ntd(const EParams &p, hipStream_t st)
         if (grid > (total + 1) / 2) grid = (total + 1) / 2;
     }
     // one of the two instantiations works (the range check's flag), the other exits
-    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, false>), dim3((unsigned)grid), dim3(256), 0, st, p, (uint32_t)K,
-                       (uint32_t)S, (uint32_t)total);
-    hipLaunchKernelGGL((tp_pairsum_kernel<NT, NS, RR, true>), dim3((unsigned)grid), dim3(256), 0, st, p, (uint32_t)K,
-                       (uint32_t)S, (uint32_t)total);
+    const hipError_t e = launch(tp_pairsum_kernel<NT, NS, RR, false>, (unsigned)grid, 256, 0, st, p, (uint32_t)K,
+                                (uint32_t)S, (uint32_t)total);
+    if (e != hipSuccess) return e;
+    return launch(tp_pairsum_kernel<NT, NS, RR, true>, (unsigned)grid, 256, 0, st, p, (uint32_t)K, (uint32_t)S,
+                  (uint32_t)total);
 }
 
 template <int NT, int RR>
-void launch_ntr(const EParams &p, hipStream_t st)
+hipError_t launch_ntr(const EParams &p, hipStream_t st)
 {
     switch (p.D) {   // distance-vector components D + 2, in pairs
-    case 1: case 2: launch_ntd<NT, 2, RR>(p, st); break;
-    case 3: case 4: launch_ntd<NT, 3, RR>(p, st); break;
-    case 5: case 6: launch_ntd<NT, 4, RR>(p, st); break;
-    default: launch_ntd<NT, 5, RR>(p, st); break;
+    case 1: case 2: return launch_ntd<NT, 2, RR>(p, st);
+    case 3: case 4: return launch_ntd<NT, 3, RR>(p, st);
+    case 5: case 6: return launch_ntd<NT, 4, RR>(p, st);
+    default: return launch_ntd<NT, 5, RR>(p, st);
     }
 }
 
 template <int NT>
-void launch_nt(const EParams &p, hipStream_t st)
+hipError_t launch_nt(const EParams &p, hipStream_t st)
 {
-    if (p.R <= 1) launch_ntr<NT, 1>(p, st);
-    else if (p.R == 2) launch_ntr<NT, 2>(p, st);
-    else launch_ntr<NT, 3>(p, st);
+    if (p.R <= 1) return launch_ntr<NT, 1>(p, st);
+    if (p.R == 2) return launch_ntr<NT, 2>(p, st);
+    return launch_ntr<NT, 3>(p, st);
 }
 
 // Certified order of two pair masses m^2(a, b) against m^2(c, d): +1 if
@@ -1080,23 +1083,17 @@ __global__ void tp_coords_kernel(CParams c)
 
 hipError_t launch_pairsums(const EParams &p, hipStream_t st)
 {
-    hipLaunchKernelGGL(tp_range_kernel, dim3((unsigned)((p.n + 255) / 256)), dim3(256), 0, st, p);
-    const int nt = p.C / 32;
-    switch (nt) {
-    case 1: launch_nt<1>(p, st); break;
-    case 2: launch_nt<2>(p, st); break;
-    case 4: launch_nt<4>(p, st); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    if (p.C != 32 && p.C != 64 && p.C != 128) return hipErrorInvalidValue;
+    const hipError_t e = launch(tp_range_kernel, (unsigned)((p.n + 255) / 256), 256, 0, st, p);
+    if (e != hipSuccess) return e;
+    return p.C == 32 ? launch_nt<1>(p, st) : p.C == 64 ? launch_nt<2>(p, st) : launch_nt<4>(p, st);
 }
 
 hipError_t launch_coords(const CParams &c, int dtype, hipStream_t st)
 {
     const int64_t grid = (c.n + 255) / 256;
-    if (dtype == 0) hipLaunchKernelGGL(tp_coords_kernel<float>, dim3((unsigned)grid), dim3(256), 0, st, c);
-    else hipLaunchKernelGGL(tp_coords_kernel<double>, dim3((unsigned)grid), dim3(256), 0, st, c);
-    return hipGetLastError();
+    return dtype == 0 ? launch(tp_coords_kernel<float>, (unsigned)grid, 256, 0, st, c)
+                      : launch(tp_coords_kernel<double>, (unsigned)grid, 256, 0, st, c);
 }
 
 }  // namespace tpe

@@ -10,6 +10,7 @@
 #include "tp_dword.h"
 #include "tp_exact.h"
 #include "tp_kernel.h"
+#include "tp_launch.h"
 
 namespace tpk {
 namespace {
@@ -323,16 +324,11 @@ __global__ __launch_bounds__(64) void tp_exact_kernel(const KParams kp)
 
 hipError_t launch_exact(int dtype, int mode, const KParams &kp, int grid, hipStream_t st)
 {
-#define TP_X(T, M) hipLaunchKernelGGL((tp_exact_kernel<T, M>), dim3(grid), dim3(64), 0, st, kp)
-    if (dtype == 0) {
-        if (mode == 0) TP_X(float, 0);
-        else TP_X(float, 1);
-    } else {
-        if (mode == 0) TP_X(double, 0);
-        else TP_X(double, 1);
-    }
-#undef TP_X
-    return hipGetLastError();
+    if (dtype == 0)
+        return mode == 0 ? launch(tp_exact_kernel<float, 0>, grid, 64, 0, st, kp)
+                         : launch(tp_exact_kernel<float, 1>, grid, 64, 0, st, kp);
+    return mode == 0 ? launch(tp_exact_kernel<double, 0>, grid, 64, 0, st, kp)
+                     : launch(tp_exact_kernel<double, 1>, grid, 64, 0, st, kp);
 }
 
 }  // namespace tpk

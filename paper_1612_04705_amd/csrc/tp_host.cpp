@@ -41,11 +41,20 @@ int fail(int code, const std::string &msg)
     return code;
 }
 
-#define TP_HIP(call)                                                                    \
-    do {                                                                                \
-        hipError_t e_ = (call);                                                         \
-        if (e_ != hipSuccess)                                                           \
-            return fail(TP_EHIP, std::string(#call) + ": " + hipGetErrorString(e_));    \
+// A failed runtime call, reported by the status: its error is taken off the
+// runtime's record, where the next caller to look (this library's or another's)
+// would take it for its own.
+int hip_fail(int code, const std::string &msg)
+{
+    (void)hipGetLastError();
+    return fail(code, msg);
+}
+
+#define TP_HIP(call)                                                                        \
+    do {                                                                                    \
+        hipError_t e_ = (call);                                                             \
+        if (e_ != hipSuccess)                                                               \
+            return hip_fail(TP_EHIP, std::string(#call) + ": " + hipGetErrorString(e_));    \
     } while (0)
 
 // The exact-tier list holds one entry per event of a launch (the plan's
@@ -225,7 +234,7 @@ bool capturing(hipStream_t st)
 int new_workspace(uint64_t cap, hipStream_t st, Workspace &w)
 {
     const size_t bytes = cap * sizeof(uint64_t) + 256 + REP_WORDS * sizeof(uint64_t);
-    if (hipMalloc(&w.buf, bytes) != hipSuccess) return fail(TP_ENOMEM, "workspace allocation failed");
+    if (hipMalloc(&w.buf, bytes) != hipSuccess) return hip_fail(TP_ENOMEM, "workspace allocation failed");
     w.cap = cap;
     w.xlist = static_cast<uint64_t *>(w.buf);
     w.xcount = reinterpret_cast<uint32_t *>(static_cast<char *>(w.buf) + cap * sizeof(uint64_t));
@@ -690,12 +699,12 @@ int build_plan(Device &d, const std::vector<Req> &rq, int mode, hipStream_t st, 
     const size_t tot = foff + fb;
     if (hipMalloc(&p->dbuf, tot) != hipSuccess) {
         delete p;
-        return fail(TP_ENOMEM, "plan table allocation failed");
+        return hip_fail(TP_ENOMEM, "plan table allocation failed");
     }
     if (hipHostMalloc(&p->pinned, tot, hipHostMallocDefault) != hipSuccess) {
         hipFree(p->dbuf);
         delete p;
-        return fail(TP_ENOMEM, "pinned staging allocation failed");
+        return hip_fail(TP_ENOMEM, "pinned staging allocation failed");
     }
     std::memcpy(p->pinned, p->hs.data(), sb);
     std::memcpy(static_cast<char *>(p->pinned) + eoff, p->hedges.data(), eb);
@@ -769,7 +778,7 @@ int side_streams(Device &d)
         d.side.clear();
         d.join.clear();
         d.fork = nullptr;
-        return fail(TP_EHIP, std::string("side streams: ") + hipGetErrorString(e));
+        return hip_fail(TP_EHIP, std::string("side streams: ") + hipGetErrorString(e));
     }
     return TP_OK;
 }
@@ -1062,7 +1071,7 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
             g_timing.on = was_on;
             hipStreamDestroy(cap);
             if (rc) return rc;
-            if (ee != hipSuccess) return fail(TP_EHIP, std::string("graph capture: ") + hipGetErrorString(ee));
+            if (ee != hipSuccess) return hip_fail(TP_EHIP, std::string("graph capture: ") + hipGetErrorString(ee));
             ge.graph = g;
             TP_HIP(hipGraphInstantiate(&ge.exec, g, nullptr, nullptr, 0));
             it = d.graphs.emplace(gk, ge).first;
@@ -1367,7 +1376,7 @@ int tp_autotune(const tp_sample *samples, int32_t nsamples, int32_t precision, v
             if (hipMalloc(&d.scratch_counts, words * 8) != hipSuccess) {
                 d.scratch_counts = nullptr;
                 d.scratch_words = 0;
-                return fail(TP_ENOMEM, "autotune scratch allocation failed");
+                return hip_fail(TP_ENOMEM, "autotune scratch allocation failed");
             }
             d.scratch_words = words;
         }
@@ -1699,7 +1708,7 @@ int tp_pairsums(const float *coords, int32_t dims, int64_t ld, int64_t n, double
             // zero once; each launch that sets the flag clears it when done
             if (hipMalloc(&f, 2 * sizeof(uint32_t)) != hipSuccess) {
                 d.eflag.erase(st);
-                return fail(TP_ENOMEM, "flag allocation failed");
+                return hip_fail(TP_ENOMEM, "flag allocation failed");
             }
             TP_HIP(hipMemset(f, 0, 2 * sizeof(uint32_t)));
         }

@@ -15,6 +15,7 @@
 #include <mutex>
 
 #include "tp_kernel.h"
+#include "tp_launch.h"
 #include "tp_noalloc.h"
 
 namespace tpk {
@@ -77,8 +78,7 @@ hipError_t launch_noalloc_setup(const KSample &k, const double *edges, int nedge
     a.nedges = nedges;
     a.nrep = (int32_t)nrep;
     for (int i = 0; i < nedges; ++i) a.edges[i] = edges[i];
-    hipLaunchKernelGGL(tp_noalloc_setup, dim3((unsigned)(1 + nrep / 4096)), dim3(256), 0, st, a, base);
-    return hipGetLastError();
+    return launch(tp_noalloc_setup, (unsigned)(1 + nrep / 4096), 256, 0, st, a, base);
 }
 
 }  // namespace tpk

@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include "tp_kernel.h"
+#include "tp_launch.h"
 
 namespace tpk {
 namespace {
@@ -1154,42 +1155,37 @@ __global__ __launch_bounds__(256) void tp_probe_kernel(const KSample k, float *d
 // ------------------------------------------------------------------ launchers
 namespace {
 template <typename T, int P, int M, int EPL, int K0, int K1>
-void launch_one(bool ord, const KParams &kp, int grid, int block, size_t lds, hipStream_t st)
+hipError_t launch_one(bool ord, const KParams &kp, int grid, int block, size_t lds, hipStream_t st)
 {
     // with a plane angle binned, the float32-sign variant is the float64 one
     constexpr int PE = (K0 == AX_ABSPHI || K1 == AX_ABSPHI) ? 0 : P;
     // the first pass takes the ordering of identical particles as a
     // compile-time step; the full evaluation decides it per sample
     if (lean_pass<T, M, K0, K1>() && ord)
-        hipLaunchKernelGGL((tp_pass_kernel<T, PE, M, EPL, K0, K1, true>), dim3(grid), dim3(block), lds, st, kp);
-    else
-        hipLaunchKernelGGL((tp_pass_kernel<T, PE, M, EPL, K0, K1, false>), dim3(grid), dim3(block), lds, st, kp);
+        return launch(tp_pass_kernel<T, PE, M, EPL, K0, K1, true>, grid, block, lds, st, kp);
+    return launch(tp_pass_kernel<T, PE, M, EPL, K0, K1, false>, grid, block, lds, st, kp);
 }
 
 template <typename T, int P, int M, int K0, int K1>
-void launch_epl(int epl, bool ord, const KParams &kp, int grid, int block, size_t lds, hipStream_t st)
+hipError_t launch_epl(int epl, bool ord, const KParams &kp, int grid, int block, size_t lds, hipStream_t st)
 {
     if constexpr (sizeof(T) == 4) {
-        if (epl >= 4) {
-            launch_one<T, P, M, 4, K0, K1>(ord, kp, grid, block, lds, st);
-            return;
-        }
+        if (epl >= 4) return launch_one<T, P, M, 4, K0, K1>(ord, kp, grid, block, lds, st);
     }
-    if (epl >= 2) launch_one<T, P, M, 2, K0, K1>(ord, kp, grid, block, lds, st);
-    else launch_one<T, P, M, 1, K0, K1>(ord, kp, grid, block, lds, st);
+    if (epl >= 2) return launch_one<T, P, M, 2, K0, K1>(ord, kp, grid, block, lds, st);
+    return launch_one<T, P, M, 1, K0, K1>(ord, kp, grid, block, lds, st);
 }
 
 template <typename T, int P, int M>
-bool launch_scheme(int k0, int k1, int epl, bool ord, const KParams &kp, int grid, int block, size_t lds,
-                   hipStream_t st)
+hipError_t launch_scheme(int k0, int k1, int epl, bool ord, const KParams &kp, int grid, int block, size_t lds,
+                         hipStream_t st)
 {
     if constexpr (M == 1) {
-        if (k0 != AX_NONE || k1 != AX_NONE) return false;
-        launch_epl<T, P, M, AX_NONE, AX_NONE>(epl, ord, kp, grid, block, lds, st);
-        return true;
+        if (k0 != AX_NONE || k1 != AX_NONE) return hipErrorInvalidValue;
+        return launch_epl<T, P, M, AX_NONE, AX_NONE>(epl, ord, kp, grid, block, lds, st);
     } else {
 #define TP_CASE(A, B)                                                          \
-    case A * 4 + B: launch_epl<T, P, M, A, B>(epl, ord, kp, grid, block, lds, st); return true;
+    case A * 4 + B: return launch_epl<T, P, M, A, B>(epl, ord, kp, grid, block, lds, st);
         switch (k0 * 4 + k1) {
             TP_CASE(AX_NONE, AX_NONE)
             TP_CASE(AX_ABSPHI, AX_NONE)
@@ -1203,7 +1199,7 @@ bool launch_scheme(int k0, int k1, int epl, bool ord, const KParams &kp, int gri
             TP_CASE(AX_ABSCOS, AX_ABSPHI)
             TP_CASE(AX_ABSCOS, AX_MASS)
             TP_CASE(AX_ABSCOS, AX_ABSCOS)
-        default: return false;
+        default: return hipErrorInvalidValue;
         }
 #undef TP_CASE
     }
@@ -1214,28 +1210,21 @@ hipError_t launch_probe(const KSample &k, float *det32, float *bound32, double *
                         hipStream_t st)
 {
     const int64_t grid = (k.n + 255) / 256;
-    hipLaunchKernelGGL(tp_probe_kernel, dim3((unsigned)grid), dim3(256), 0, st, k, det32, bound32, det64, scale64);
-    return hipGetLastError();
+    return launch(tp_probe_kernel, (unsigned)grid, 256, 0, st, k, det32, bound32, det64, scale64);
 }
 
 hipError_t launch_pass(int dtype, int prec, int mode, int epl, int k0, int k1, bool ord, const KParams &kp, int grid,
                        int block, size_t lds, hipStream_t st)
 {
-    bool ok;
     if (dtype == 0) {
-        if (prec == 1) {
-            ok = mode == 0 ? launch_scheme<float, 1, 0>(k0, k1, epl, ord, kp, grid, block, lds, st)
-                           : launch_scheme<float, 1, 1>(k0, k1, epl, ord, kp, grid, block, lds, st);
-        } else {
-            ok = mode == 0 ? launch_scheme<float, 0, 0>(k0, k1, epl, ord, kp, grid, block, lds, st)
-                           : launch_scheme<float, 0, 1>(k0, k1, epl, ord, kp, grid, block, lds, st);
-        }
-    } else {
-        ok = mode == 0 ? launch_scheme<double, 0, 0>(k0, k1, epl, ord, kp, grid, block, lds, st)
-                       : launch_scheme<double, 0, 1>(k0, k1, epl, ord, kp, grid, block, lds, st);
+        if (prec == 1)
+            return mode == 0 ? launch_scheme<float, 1, 0>(k0, k1, epl, ord, kp, grid, block, lds, st)
+                             : launch_scheme<float, 1, 1>(k0, k1, epl, ord, kp, grid, block, lds, st);
+        return mode == 0 ? launch_scheme<float, 0, 0>(k0, k1, epl, ord, kp, grid, block, lds, st)
+                         : launch_scheme<float, 0, 1>(k0, k1, epl, ord, kp, grid, block, lds, st);
     }
-    if (!ok) return hipErrorInvalidValue;
-    return hipGetLastError();
+    return mode == 0 ? launch_scheme<double, 0, 0>(k0, k1, epl, ord, kp, grid, block, lds, st)
+                     : launch_scheme<double, 0, 1>(k0, k1, epl, ord, kp, grid, block, lds, st);
 }
 
 }  // namespace tpk

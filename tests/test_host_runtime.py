@@ -1,0 +1,94 @@
+"""The host runtime's bookkeeping (csrc/tp_host.cpp on a HIP runtime of host memory, tests/host/runtime_harness.cpp):
+what a failed call leaves behind.  CPU only."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1612_04705_amd import synth, tpasym
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1612_04705_amd", "csrc")
+SRC = os.path.join(ROOT, "tests", "host", "runtime_harness.cpp")
+OUT = os.path.join(ROOT, "tests", "_build", "libruntime_harness.so")
+VP, P = ctypes.c_void_p, ctypes.POINTER
+PHI, MASS = [synth.absphi_axis(10)], [synth.mass_axis((0, 1), 900.0, 1800.0, 8)]
+
+
+@pytest.fixture(scope="module")
+def built():
+    os.makedirs(os.path.dirname(OUT), exist_ok=True)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC, SRC, "-o", OUT], check=True)
+    lib = ctypes.CDLL(OUT)
+    lib.fk_fail.argtypes = [ctypes.c_char_p, ctypes.c_int]
+    lib.fk_bytes.restype = lib.fk_blocks.restype = ctypes.c_int64
+    lib.fk_live.argtypes = [VP]
+    lib.fk_launch_list.restype = lib.fk_launch_samples.restype = lib.fk_stream.restype = lib.fk_end.restype = VP
+    lib.fk_begin.argtypes = lib.fk_end.argtypes = lib.fk_replay.argtypes = [VP]
+    lib.tp_strerror.restype = ctypes.c_char_p
+    lib.tp_bin.argtypes = [P(tpasym._Events), P(tpasym._Channel), P(tpasym._Binning), ctypes.c_int32, VP, VP, VP]
+    lib.tp_bin_checked.argtypes = lib.tp_bin.argtypes + [P(ctypes.c_uint64)]
+    lib.tp_batch.argtypes = [P(tpasym._Sample), ctypes.c_int32, ctypes.c_int32, P(tpasym.Tuning), ctypes.c_int32, VP]
+    return lib
+
+
+@pytest.fixture
+def hr(built):
+    built.fk_fail(b"", 0)
+    yield built
+    built.fk_fail(b"", 0)
+    built.fk_pending()
+    assert built.tp_release() == 0
+
+
+class Sample:
+    """Counters of its own; the events' memory is not read."""
+    chan = tpasym.channel((0, 1, 2))
+
+    def __init__(self, n, axes=PHI, at=0x10000):
+        self.n, self.bn = n, tpasym.Binning(axes)
+        self.ev = tpasym._Events(n=n, dtype=tpasym.TP_F32, tag=at)
+        for k in range(16):
+            self.ev.p[k] = at
+        self.counts, self.stats = np.zeros(self.bn.nrows * 4, np.uint64), np.zeros(8, np.uint64)
+
+    def args(self, stream=None):
+        return (ctypes.byref(self.ev), ctypes.byref(self.chan), ctypes.byref(self.bn.b), 1, self.counts.ctypes.data,
+                self.stats.ctypes.data, stream)
+
+    def holds(self, calls):
+        return self.counts[:2].tolist() == [calls * (self.n - 1), calls] and int(self.stats[0]) == calls * self.n
+
+    def clear(self):
+        self.counts[:] = self.stats[:] = 0
+
+
+def batch(samples):
+    arr = (tpasym._Sample * len(samples))()
+    for a, s in zip(arr, samples):
+        a.ev, a.ch, a.bn, a.counts, a.stats = s.ev, s.chan, s.bn.b, s.counts.ctypes.data, s.stats.ctypes.data
+    return arr
+
+
+def test_calls_and_graphs(hr):
+    a, b = Sample(5000), Sample(50000, MASS, 0x20000)
+    un = ctypes.c_uint64(7)
+    assert hr.tp_bin(*a.args()) == 0 and hr.tp_bin_checked(*a.args(), ctypes.byref(un)) == 0 and un.value == 0
+    arr = batch([a, b])
+    for flags in (0, 1, 1):
+        assert hr.tp_batch(arr, 2, 1, None, flags, None) == 0
+    assert a.holds(5) and b.holds(3)
+    assert hr.tp_release() == 0 and hr.fk_blocks() == 0
+
+
+@pytest.mark.parametrize("name,after", [("hipMalloc", 1), ("hipMalloc", 2), ("hipHostMalloc", 1), ("hipMemcpyAsync", 1),
+                                        ("launch_pass", 1), ("launch_exact", 1)])
+def test_reported_errors_are_not_left_unread(hr, name, after):
+    """The error that a status reports is not found again by the process's next look at the runtime's last error."""
+    a = Sample(50000)
+    hr.fk_fail(name.encode(), after)
+    assert hr.tp_bin(*a.args()) != 0
+    assert hr.fk_pending() == 0
