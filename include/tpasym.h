@@ -27,8 +27,11 @@
  *   - Counts and statistics ACCUMULATE (+=): zero them once, then chunks,
  *     batches or shards simply add up.
  *   - Return value: TP_OK (0) or a negative tp_status.  All argument checks run
- *     on the host before anything is enqueued; on error nothing is enqueued and
- *     no output is touched.  tp_strerror() gives a thread-local message.
+ *     on the host before anything is enqueued; on any error but TP_EHIP nothing is
+ *     enqueued and no output is touched.  TP_EHIP: a HIP runtime call failed, with
+ *     part of the work enqueued perhaps, so counts, statistics and per-event
+ *     outputs of that call are to be discarded; calls after it are not affected.
+ *     tp_strerror() gives a thread-local message.
  *   - Events whose decision needs the exact tier beyond its range (a single
  *     event whose nonzero components span more than 2^107 (float64) / 2^136
  *     (float32) in magnitude) are counted in tp_stats.n_unresolved and in no

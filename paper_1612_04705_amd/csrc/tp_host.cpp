@@ -91,7 +91,12 @@ struct Workspace {
     uint32_t *xdone = nullptr;
     uint64_t *rep = nullptr;   // replicated counters
     uint64_t cap = 0;      // list entries
+    // A launch over this workspace was begun and its exact-tier kernel, which leaves
+    // the list and the replicas empty, not enqueued: they may hold that launch's events.
+    bool dirty = false;
 };
+
+constexpr size_t COUNTER_BYTES = 256 + REP_WORDS * sizeof(uint64_t);   // list counters and replicas
 
 // List capacity for a launch over ``vtotal`` virtual events.
 uint64_t list_capacity(int64_t vtotal)
@@ -233,23 +238,30 @@ bool capturing(hipStream_t st)
 // A deferral workspace of ``cap`` list entries; its counters are cleared on ``st``.
 int new_workspace(uint64_t cap, hipStream_t st, Workspace &w)
 {
-    const size_t bytes = cap * sizeof(uint64_t) + 256 + REP_WORDS * sizeof(uint64_t);
+    const size_t bytes = cap * sizeof(uint64_t) + COUNTER_BYTES;
     if (hipMalloc(&w.buf, bytes) != hipSuccess) return hip_fail(TP_ENOMEM, "workspace allocation failed");
     w.cap = cap;
     w.xlist = static_cast<uint64_t *>(w.buf);
     w.xcount = reinterpret_cast<uint32_t *>(static_cast<char *>(w.buf) + cap * sizeof(uint64_t));
     w.xdone = w.xcount + 1;
     w.rep = reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(w.xcount) + 256);
-    TP_HIP(hipMemsetAsync(w.xcount, 0, 256 + REP_WORDS * sizeof(uint64_t), st));
+    TP_HIP(hipMemsetAsync(w.xcount, 0, COUNTER_BYTES, st));
     return TP_OK;
 }
 
-// The stream's workspace, grown (after the stream's earlier work) to ``cap`` entries.
-int get_workspace(Device &d, hipStream_t st, uint64_t cap, Workspace &out)
+// The stream's workspace, grown (after the stream's earlier work) to ``cap`` entries
+// and cleared if a failed launch left it dirty.
+int get_workspace(Device &d, hipStream_t st, uint64_t cap, Workspace *&out)
 {
     auto it = d.ws.find(st);
+    if (it != d.ws.end() && it->second.dirty) {
+        // the failed launch's side branches may not have been joined
+        for (hipStream_t s2 : d.side) TP_HIP(hipStreamSynchronize(s2));
+        TP_HIP(hipMemsetAsync(it->second.xcount, 0, COUNTER_BYTES, st));
+        it->second.dirty = false;
+    }
     if (it != d.ws.end() && it->second.cap >= cap) {
-        out = it->second;
+        out = &it->second;
         return TP_OK;
     }
     if (it != d.ws.end()) {
@@ -260,8 +272,7 @@ int get_workspace(Device &d, hipStream_t st, uint64_t cap, Workspace &out)
     Workspace w;
     const int rc = new_workspace(cap, st, w);
     if (rc) return rc;
-    d.ws[st] = w;
-    out = w;
+    out = &(d.ws[st] = w);
     return TP_OK;
 }
 
@@ -825,7 +836,8 @@ int launch_group(int cus, const Group &g, tp_tuning tu, int dtype, int prec, int
 // launch shape gtu[g]; only the group ``only`` when it is >= 0), then the
 // exact tier over the shared deferral list.
 int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int prec, int mode,
-                const Workspace &ws, hipStream_t st, int only = -1, uint64_t *mail = nullptr)
+                Workspace &ws, hipStream_t st, int only = -1, uint64_t *mail = nullptr,
+                bool replicas = true)
 {
     if (p.vtotal == 0) return TP_OK;
     const bool timed = g_timing.on && !g_timing.ring.empty();
@@ -836,6 +848,7 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
         e1 = pr.second;
         TP_HIP(hipEventRecord(e0, st));
     }
+    ws.dirty = true;
     KParams kp;
     std::memset(&kp, 0, sizeof kp);
     kp.samples = p.dsamples;
@@ -845,9 +858,9 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
     kp.xdone = ws.xdone;
     kp.xcap = (uint32_t)ws.cap;
     kp.mode = mode;
-    kp.rep = ws.rep;
+    kp.rep = replicas ? ws.rep : nullptr;
     kp.fold = p.hs.size() > 1 ? p.dfold : nullptr;
-    kp.nfold = ws.rep ? (int32_t)p.hfold.size() : 0;
+    kp.nfold = kp.rep ? (int32_t)p.hfold.size() : 0;
     kp.mail = mail;
     // Several scheme groups run as parallel branches (the caller's stream and
     // NSIDE side streams, in turn): their launches overlap,
@@ -924,6 +937,7 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
         std::fprintf(stderr, "\n");
     }
     TP_HIP(launch_exact(p.dtype, mode, kp, exact_grid(p.vtotal, kp.nfold), st));
+    ws.dirty = false;
     return TP_OK;
 }
 
@@ -1087,14 +1101,13 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
         }
         return end_use(*p, st);
     }
-    Workspace ws;
+    Workspace *ws = nullptr;
     rc = get_workspace(d, st, list_capacity(p->vtotal), ws);
     if (rc) return rc;
+    if (mail) *mail = take_mail();
     // a captured launch may be replayed beside this stream's own calls: it counts
     // directly
-    if (capturing(st)) ws.rep = nullptr;
-    if (mail) *mail = take_mail();
-    rc = launch_plan(d, *p, gtu, prec, mode, ws, st, -1, mail ? *mail : nullptr);
+    rc = launch_plan(d, *p, gtu, prec, mode, *ws, st, -1, mail ? *mail : nullptr, !capturing(st));
     if (rc) return rc;
     return end_use(*p, st);
 }
@@ -1415,18 +1428,18 @@ int tp_autotune(const tp_sample *samples, int32_t nsamples, int32_t precision, v
     const bool was_on = g_timing.on;
     g_timing.on = false;
     Plan *p = nullptr;
-    Workspace ws;
+    Workspace *ws = nullptr;
     rc = build_plan(d, rq, 0, st, p);
     if (!rc) rc = begin_use(*p, st);
     if (!rc) rc = get_workspace(d, st, list_capacity(p->vtotal), ws);
     // time ``trials`` runs of ``reps`` launches of group g with shape t; best run, ms per launch
     auto measure = [&](size_t g, const tp_tuning &t, int trials, int reps, float &ms) -> int {
         const std::vector<tp_tuning> gtu(p->groups.size(), t);
-        int r = launch_plan(d, *p, gtu, precision, 0, ws, st, (int)g);   // warm-up
+        int r = launch_plan(d, *p, gtu, precision, 0, *ws, st, (int)g);   // warm-up
         ms = 1e30f;
         for (int trial = 0; trial < trials && !r; ++trial) {
             TP_HIP(hipEventRecord(a, st));
-            for (int k = 0; k < reps && !r; ++k) r = launch_plan(d, *p, gtu, precision, 0, ws, st, (int)g);
+            for (int k = 0; k < reps && !r; ++k) r = launch_plan(d, *p, gtu, precision, 0, *ws, st, (int)g);
             TP_HIP(hipEventRecord(b, st));
             TP_HIP(hipEventSynchronize(b));
             float m = 0;
@@ -1438,7 +1451,7 @@ int tp_autotune(const tp_sample *samples, int32_t nsamples, int32_t precision, v
     // bring the clocks up before anything is timed
     if (!rc) {
         const std::vector<tp_tuning> gtu(p->groups.size(), cand[0]);
-        for (int k = 0; k < 5 && !rc; ++k) rc = launch_plan(d, *p, gtu, precision, 0, ws, st);
+        for (int k = 0; k < 5 && !rc; ++k) rc = launch_plan(d, *p, gtu, precision, 0, *ws, st);
         if (!rc) TP_HIP(hipStreamSynchronize(st));
     }
     // each scheme group is tuned on its own launches: every candidate briefly,

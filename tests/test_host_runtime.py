@@ -92,3 +92,37 @@ def test_reported_errors_are_not_left_unread(hr, name, after):
     hr.fk_fail(name.encode(), after)
     assert hr.tp_bin(*a.args()) != 0
     assert hr.fk_pending() == 0
+
+
+@pytest.mark.parametrize("name", ["launch_pass", "launch_exact", "hipEventRecord", "hipStreamWaitEvent"])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_failed_launch_leaves_no_counts(hr, name, flags):
+    """A batch of three schemes on parallel branches whose k-th call of one function fails, for every k that a call
+    reaches: the next call on the stream holds its own events alone."""
+    ss = [Sample(50000, PHI), Sample(200000, MASS, 0x20000), Sample(70000, [synth.abscos_axis(0, 5)], 0x30000)]
+    arr = batch(ss)
+    assert hr.tp_batch(arr, 3, 1, None, 0, None) == 0
+    reached = 0
+    for k in range(1, 20):
+        for s in ss:
+            s.clear()
+        hr.fk_fail(name.encode(), k)
+        rc = hr.tp_batch(arr, 3, 1, None, flags, None)
+        hr.fk_fail(b"", 0)
+        if rc == 0:
+            assert all(s.holds(1) for s in ss)
+            break
+        reached += 1
+        for s in ss:
+            s.clear()
+        assert hr.tp_batch(arr, 3, 1, None, 0, None) == 0
+        assert all(s.holds(1) for s in ss), k
+    assert rc == 0 and reached >= 1
+
+
+def test_failed_tuning_leaves_no_counts(hr):
+    a = Sample(50000)
+    hr.fk_fail(b"launch_exact", 30)
+    assert hr.tp_autotune(batch([a]), 1, 1, None, ctypes.byref(tpasym.Tuning())) != 0
+    hr.fk_fail(b"", 0)
+    assert hr.tp_bin(*a.args()) == 0 and a.holds(1)
