@@ -186,7 +186,7 @@ int tp_bin(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int3
  * tp_bin_checked -- tp_bin, then a wait for the stream's work.
  *   unresolved: host; stats->n_unresolved after the call (what earlier calls
  *               added included).  The last kernel stores it in host memory, so
- *               no copy follows the wait.  Not under graph capture.
+ *               no copy follows the wait.  Under graph capture: TP_EUNSUPPORTED.
  */
 int tp_bin_checked(const tp_events *ev, const tp_channel *ch, const tp_binning *bn, int32_t precision,
                    uint64_t *counts, tp_stats *stats, void *stream, uint64_t *unresolved);

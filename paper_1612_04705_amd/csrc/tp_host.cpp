@@ -189,15 +189,38 @@ std::map<int, Device> g_dev;
 
 // Host words that a launch's last kernel stores a count in, one page of them for
 // the process, a cache line each: taken by a call and given back once the launch
-// has ended.  All calls beyond MAILS at a time read the count by a copy.
+// has ended.  All calls beyond MAILS at a time read the count by a copy.  A call
+// that fails after its last kernel was enqueued has not waited for it: its word is
+// owed, and free once that kernel has written it.
 constexpr int MAILS = 32;
 constexpr int MAIL_WORDS = 16;
+constexpr uint64_t MAIL_UNWRITTEN = ~uint64_t(0);
 uint64_t *g_mail = nullptr;
 std::vector<int> g_mail_free;
+std::vector<uint64_t *> g_mail_owed;
+
+void give_mail(uint64_t *m) { g_mail_free.push_back((int)((m - g_mail) / MAIL_WORDS)); }
+
+uint64_t read_mail(const uint64_t *m) { return *static_cast<const volatile uint64_t *>(m); }
+
+// Owed words that have been written are free (under g_mu).
+void collect_mail()
+{
+    for (size_t i = 0; i < g_mail_owed.size();) {
+        if (read_mail(g_mail_owed[i]) == MAIL_UNWRITTEN) {
+            ++i;
+            continue;
+        }
+        give_mail(g_mail_owed[i]);
+        g_mail_owed[i] = g_mail_owed.back();
+        g_mail_owed.pop_back();
+    }
+}
 
 // A free word (under g_mu), or null.
 uint64_t *take_mail()
 {
+    collect_mail();
     if (!g_mail) {
         void *m = nullptr;
         if (hipHostMalloc(&m, MAILS * MAIL_WORDS * sizeof(uint64_t), hipHostMallocPortable) != hipSuccess) {
@@ -210,10 +233,10 @@ uint64_t *take_mail()
     if (g_mail_free.empty()) return nullptr;
     const int i = g_mail_free.back();
     g_mail_free.pop_back();
-    return g_mail + i * MAIL_WORDS;
+    uint64_t *m = g_mail + i * MAIL_WORDS;
+    *static_cast<volatile uint64_t *>(m) = MAIL_UNWRITTEN;
+    return m;
 }
-
-void give_mail(uint64_t *m) { g_mail_free.push_back((int)((m - g_mail) / MAIL_WORDS)); }
 
 TimingState g_timing;
 
@@ -1046,7 +1069,7 @@ int current_device(int &id)
 }
 
 // ``mail`` (one request only): gets a host word that holds stats->n_unresolved
-// once the launch has ended, or null.
+// once the launch has ended, or null; of no use to the caller on an error.
 int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning, int flags, hipStream_t st,
         uint64_t **mail = nullptr)
 {
@@ -1108,8 +1131,13 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
     // a captured launch may be replayed beside this stream's own calls: it counts
     // directly
     rc = launch_plan(d, *p, gtu, prec, mode, *ws, st, -1, mail ? *mail : nullptr, !capturing(st));
-    if (rc) return rc;
-    return end_use(*p, st);
+    if (rc) {
+        if (mail && *mail) give_mail(*mail);    // its kernel was not enqueued
+        return rc;
+    }
+    rc = end_use(*p, st);
+    if (rc && mail && *mail) g_mail_owed.push_back(*mail);
+    return rc;
 }
 
 // exact ratio num/den of integers, rounded (long double division, then to double)
@@ -1234,17 +1262,19 @@ int tp_bin_checked(const tp_events *ev, const tp_channel *ch, const tp_binning *
 {
     if (!unresolved) return fail(TP_EINVAL, "unresolved is required");
     const hipStream_t st = static_cast<hipStream_t>(stream);
+    if (capturing(st)) return fail(TP_EUNSUPPORTED, "tp_bin_checked waits for its stream, which is being captured");
     uint64_t *mail = nullptr;
     const int rc = bin_one(ev, ch, bn, precision, counts, stats, stream, &mail);
-    if (rc) return rc;      // a word taken by a launch that failed is not used again
-    TP_HIP(hipStreamSynchronize(st));
-    if (!mail) {
-        TP_HIP(hipMemcpy(unresolved, &stats->n_unresolved, sizeof *unresolved, hipMemcpyDeviceToHost));
-        return TP_OK;
+    if (rc) return rc;
+    const hipError_t e = hipStreamSynchronize(st);
+    if (mail) {
+        *unresolved = read_mail(mail);
+        std::lock_guard<std::mutex> lk(g_mu);
+        if (e == hipSuccess) give_mail(mail);
+        else g_mail_owed.push_back(mail);
     }
-    *unresolved = *static_cast<volatile uint64_t *>(mail);
-    std::lock_guard<std::mutex> lk(g_mu);
-    give_mail(mail);
+    TP_HIP(e);
+    if (!mail) TP_HIP(hipMemcpy(unresolved, &stats->n_unresolved, sizeof *unresolved, hipMemcpyDeviceToHost));
     return TP_OK;
 }
 
@@ -1628,6 +1658,7 @@ int tp_release(void)
         if (d.fork) hipEventDestroy(d.fork);
     }
     g_dev.clear();
+    collect_mail();
     if ((int)g_mail_free.size() == MAILS) {     // no call is still reading its word
         hipHostFree(g_mail);
         g_mail = nullptr;

@@ -126,3 +126,39 @@ def test_failed_tuning_leaves_no_counts(hr):
     assert hr.tp_autotune(batch([a]), 1, 1, None, ctypes.byref(tpasym.Tuning())) != 0
     hr.fk_fail(b"", 0)
     assert hr.tp_bin(*a.args()) == 0 and a.holds(1)
+
+
+@pytest.mark.parametrize("name", ["hipMalloc", "launch_pass", "launch_exact", "hipEventRecord", "hipStreamSynchronize"])
+def test_failed_checked_calls_keep_no_host_word(hr, name):
+    """40 checked calls that fail, more than there are host words: the next one still gets its count through one, and
+    tp_release gives their page back."""
+    a, un, held = Sample(5000), ctypes.c_uint64(), hr.fk_blocks()
+    assert hr.tp_bin_checked(*a.args(), ctypes.byref(un)) == 0
+    for k in range(40):
+        b = Sample(5000 + k, at=0x20000 + 0x100 * k) if name == "hipMalloc" else a
+        hr.fk_fail(name.encode(), 1)
+        assert hr.tp_bin_checked(*b.args(), ctypes.byref(un)) != 0
+        hr.fk_fail(b"", 0)
+    a.clear()
+    a.stats[6] = 3
+    hr.fk_fail(b"hipMemcpy", 1)             # not called: no copy of the count
+    assert hr.tp_bin_checked(*a.args(), ctypes.byref(un)) == 0
+    hr.fk_fail(b"", 0)
+    assert un.value == 3 and a.holds(1)
+    assert hr.tp_release() == 0 and hr.fk_blocks() == held
+
+
+def test_checked_call_refused_under_capture(hr):
+    """A checked call waits for its stream, which cannot be waited for while it is captured: refused with nothing
+    recorded and no host word taken."""
+    a, un, st, held = Sample(5000), ctypes.c_uint64(), hr.fk_stream(), hr.fk_blocks()
+    assert hr.tp_bin_checked(*a.args(st), ctypes.byref(un)) == 0
+    n = hr.fk_launch_count()
+    hr.fk_begin(st)
+    for _ in range(40):
+        assert hr.tp_bin_checked(*a.args(st), ctypes.byref(un)) == -2
+    assert hr.fk_launch_count() == n and hr.fk_pending() == 0
+    g = hr.fk_end(st)
+    hr.fk_replay(g)
+    assert a.holds(1)
+    assert hr.tp_release() == 0 and hr.fk_blocks() == held
