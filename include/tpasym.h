@@ -32,6 +32,12 @@
  *     part of the work enqueued perhaps, so counts, statistics and per-event
  *     outputs of that call are to be discarded; calls after it are not affected.
  *     tp_strerror() gives a thread-local message.
+ *   - Graph capture: tp_compute, tp_bin and tp_batch may be called on a stream that
+ *     is being captured into a graph of the caller's, with or without calls before.
+ *     The graph uses memory that the library keeps for it until tp_release(), apart
+ *     from what the stream's own calls use, so a replay may overlap any other call.
+ *     Calls captured on one stream share that memory: replays of two graphs captured
+ *     on the same stream must not overlap.
  *   - Events whose decision needs the exact tier beyond its range (a single
  *     event whose nonzero components span more than 2^107 (float64) / 2^136
  *     (float32) in magnitude) are counted in tp_stats.n_unresolved and in no
@@ -324,7 +330,8 @@ int tp_timing_reset(void);
 int tp_timing_read(double *avg_ms, int64_t *launches);
 
 /* Release per-device internal state (workspaces, plans, graphs, side streams
- * and their events, pair-sum flags); later calls recreate what they need.  The
+ * and their events, pair-sum flags); later calls recreate what they need.  A
+ * caller's graph that holds captured calls must not be replayed after it.  The
  * allocation-free entry point's device array stays until the process ends. */
 int tp_release(void);
 
@@ -373,7 +380,9 @@ int tp_coords(const tp_events *ev, const int32_t *masks, int32_t ncoord, double 
  * (scaled squared distance > 1024) or is not finite, the launch instead forms
  * the distances of every chunk of pairs that holds such an event as direct
  * float32 differences of the coordinates (slower, accurate at any distance).
- * Calls on one stream share a two-word device flag of the library.
+ * Calls on one stream share a two-word device flag of the library, which the
+ * first of them allocates: capture a later one, and order its graph's replays
+ * with the stream's own calls.
  * psi enters the matrix cores again as two float16 terms (truncation
  * of psi * 2^14 and of the remainder: together within 2^-20 of psi,
  * relative); the 0/1 columns are exact in float16, products are accumulated

@@ -135,6 +135,7 @@ struct Plan {
     hipEvent_t last_use = nullptr;
     hipStream_t last_stream = nullptr;
     bool used = false;
+    bool captured = false;       // a graph of a caller's points to the tables: kept, and not in the list of the least used
     std::list<uint64_t>::iterator lru_pos;
     std::vector<uint64_t> graph_keys;   // graphs captured with this plan's tables
 };
@@ -151,9 +152,31 @@ struct TimingState {
     size_t next = 0, used = 0;
 };
 
+// Scheme groups of one launch run on parallel branches: the caller's stream and up
+// to NSIDE side streams (default priority), forked from and joined back into the
+// caller's stream by events.
+constexpr int NSIDE = 3;
+struct Sides {
+    std::vector<hipStream_t> side;
+    std::vector<hipEvent_t> join;
+    hipEvent_t fork = nullptr;
+};
+
+// What the calls captured on one stream into graphs of the caller's use in place of
+// the stream's own: a replay may run beside the stream's other calls, or after they
+// have grown their workspace, and the side streams stay in the capture until it
+// ends.  A list that a later capture finds too short is kept for the graphs that
+// point to it; capacities are powers of two, so the lists of a stream take at most
+// twice the longest.
+struct Captured {
+    std::vector<Workspace> ws;
+    Sides sides;
+};
+
 struct Device {
     int cus = 256;
     std::map<hipStream_t, Workspace> ws;
+    std::map<hipStream_t, Captured> captured;
     std::unordered_map<uint64_t, Plan *> plans;
     std::list<uint64_t> lru;
     std::unordered_map<uint64_t, GraphEntry> graphs;
@@ -162,15 +185,9 @@ struct Device {
     uint64_t *scratch_counts = nullptr;   // autotune sink
     size_t scratch_words = 0;
     std::map<hipStream_t, uint32_t *> eflag;   // pair sums per stream: range flag, workgroup count
-    // scheme groups of one launch run on parallel branches: the caller's
-    // stream and up to NSIDE side streams (default priority), forked from and
-    // joined back into the caller's stream by events
-    std::vector<hipStream_t> side;
-    std::vector<hipEvent_t> join;
-    hipEvent_t fork = nullptr;
+    Sides sides;
 };
 
-constexpr int NSIDE = 3;
 // Workgroups per CU, at most, of a scheme group running beside the largest
 // (batched 64-sample workload: 1.284 against 1.299 ms per step uncapped, 1.286
 // with 2; same box, three rounds each).
@@ -255,8 +272,35 @@ Device &device(int id)
 bool capturing(hipStream_t st)
 {
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
 }
+
+// While a stream is being captured the thread may not allocate or wait, unless its
+// capture mode is relaxed.
+struct Relaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool on;
+    explicit Relaxed(bool on_) : on(on_)
+    {
+        if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    ~Relaxed()
+    {
+        if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+// A stream of its own for what a captured call prepares: uploads and clears, which
+// must not become part of the graph.
+struct OwnStream {
+    hipStream_t st = nullptr;
+    ~OwnStream()
+    {
+        if (st) hipStreamDestroy(st);
+    }
+};
 
 // A deferral workspace of ``cap`` list entries; its counters are cleared on ``st``.
 int new_workspace(uint64_t cap, hipStream_t st, Workspace &w)
@@ -279,7 +323,7 @@ int get_workspace(Device &d, hipStream_t st, uint64_t cap, Workspace *&out)
     auto it = d.ws.find(st);
     if (it != d.ws.end() && it->second.dirty) {
         // the failed launch's side branches may not have been joined
-        for (hipStream_t s2 : d.side) TP_HIP(hipStreamSynchronize(s2));
+        for (hipStream_t s2 : d.sides.side) TP_HIP(hipStreamSynchronize(s2));
         TP_HIP(hipMemsetAsync(it->second.xcount, 0, COUNTER_BYTES, st));
         it->second.dirty = false;
     }
@@ -296,6 +340,21 @@ int get_workspace(Device &d, hipStream_t st, uint64_t cap, Workspace *&out)
     const int rc = new_workspace(cap, st, w);
     if (rc) return rc;
     out = &(d.ws[st] = w);
+    return TP_OK;
+}
+
+// A workspace of ``cap`` entries for a call captured on ``st``, cleared on ``ps``.
+int captured_workspace(Captured &c, hipStream_t ps, uint64_t cap, Workspace *&out)
+{
+    if (c.ws.empty() || c.ws.back().cap < cap || c.ws.back().dirty) {
+        uint64_t pow2 = XCAP_MIN;
+        while (pow2 < cap) pow2 *= 2;
+        Workspace w;
+        const int rc = new_workspace(pow2, ps, w);
+        if (rc) return rc;
+        c.ws.push_back(w);
+    }
+    out = &c.ws.back();
     return TP_OK;
 }
 
@@ -661,7 +720,7 @@ int build_plan(Device &d, const std::vector<Req> &rq, int mode, hipStream_t st, 
     auto it = d.plans.find(key);
     if (it != d.plans.end()) {
         out = it->second;
-        d.lru.splice(d.lru.end(), d.lru, out->lru_pos);   // most recently used last
+        if (!out->captured) d.lru.splice(d.lru.end(), d.lru, out->lru_pos);   // most recently used last
         return TP_OK;
     }
     Plan *p = new Plan();
@@ -792,8 +851,16 @@ void defaults(tp_tuning &t, int64_t nv, int stride, int dtype)
     if (t.unroll != 1 && t.unroll != 2 && t.unroll != 4) t.unroll = 1;
 }
 
-// The device's side streams and fork/join events, created on first use.
-int side_streams(Device &d)
+void free_sides(Sides &d)
+{
+    for (hipStream_t s2 : d.side) hipStreamDestroy(s2);
+    for (hipEvent_t e2 : d.join) hipEventDestroy(e2);
+    if (d.fork) hipEventDestroy(d.fork);
+    d = Sides();
+}
+
+// The side streams and fork/join events, created on first use.
+int side_streams(Sides &d)
 {
     if (d.fork) return TP_OK;
     hipError_t e = hipSuccess;
@@ -807,11 +874,7 @@ int side_streams(Device &d)
     }
     if (e == hipSuccess) e = hipEventCreateWithFlags(&d.fork, hipEventDisableTiming);
     if (e != hipSuccess) {
-        for (hipStream_t s2 : d.side) hipStreamDestroy(s2);
-        for (hipEvent_t e2 : d.join) hipEventDestroy(e2);
-        d.side.clear();
-        d.join.clear();
-        d.fork = nullptr;
+        free_sides(d);
         return hip_fail(TP_EHIP, std::string("side streams: ") + hipGetErrorString(e));
     }
     return TP_OK;
@@ -857,13 +920,15 @@ int launch_group(int cus, const Group &g, tp_tuning tu, int dtype, int prec, int
 
 // Launch the plan's pass kernels (one per scheme group, each with its own
 // launch shape gtu[g]; only the group ``only`` when it is >= 0), then the
-// exact tier over the shared deferral list.
+// exact tier over the shared deferral list.  ``captured``: into a graph of the
+// caller's.
 int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int prec, int mode,
                 Workspace &ws, hipStream_t st, int only = -1, uint64_t *mail = nullptr,
-                bool replicas = true)
+                Captured *captured = nullptr)
 {
     if (p.vtotal == 0) return TP_OK;
-    const bool timed = g_timing.on && !g_timing.ring.empty();
+    Sides &sd = captured ? captured->sides : d.sides;
+    const bool timed = g_timing.on && !g_timing.ring.empty() && !captured;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
         auto &pr = g_timing.ring[g_timing.next];
@@ -881,7 +946,7 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
     kp.xdone = ws.xdone;
     kp.xcap = (uint32_t)ws.cap;
     kp.mode = mode;
-    kp.rep = replicas ? ws.rep : nullptr;
+    kp.rep = captured ? nullptr : ws.rep;      // a captured call counts directly
     kp.fold = p.hs.size() > 1 ? p.dfold : nullptr;
     kp.nfold = kp.rep ? (int32_t)p.hfold.size() : 0;
     kp.mail = mail;
@@ -902,9 +967,9 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
     const bool fork = only < 0 && ngroups > 1;
     bool joined[NSIDE] = {};
     if (fork) {
-        int rc = side_streams(d);
+        int rc = side_streams(sd);
         if (rc) return rc;
-        TP_HIP(hipEventRecord(d.fork, st));
+        TP_HIP(hipEventRecord(sd.fork, st));
     }
     // the largest group (usually the last to finish) on the caller's stream,
     // so that the exact tier follows it without a wait on another stream
@@ -917,8 +982,8 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
         const int lane = !fork || gi == largest ? 0 : k++ % (NSIDE + 1);
         hipStream_t gs = st;
         if (lane > 0) {
-            gs = d.side[lane - 1];
-            if (!joined[lane - 1]) TP_HIP(hipStreamWaitEvent(gs, d.fork, 0));
+            gs = sd.side[lane - 1];
+            if (!joined[lane - 1]) TP_HIP(hipStreamWaitEvent(gs, sd.fork, 0));
             joined[lane - 1] = true;
         }
         // beside the largest group, a group takes at most SIDE_WG_PER_CU
@@ -933,8 +998,8 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
     }
     for (int l = 0; l < NSIDE; ++l) {
         if (!joined[l]) continue;
-        TP_HIP(hipEventRecord(d.join[l], d.side[l]));
-        TP_HIP(hipStreamWaitEvent(st, d.join[l], 0));
+        TP_HIP(hipEventRecord(sd.join[l], sd.side[l]));
+        TP_HIP(hipStreamWaitEvent(st, sd.join[l], 0));
     }
     if (timed) {
         TP_HIP(hipEventRecord(e1, st));
@@ -942,7 +1007,7 @@ int launch_plan(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int
         g_timing.used = std::min(g_timing.used + 1, g_timing.ring.size());
     }
     static const bool debug = std::getenv("TP_DEBUG") != nullptr;
-    if (debug) {
+    if (debug && !captured) {
         // diagnostics: which events the float64 tier deferred, and at which stage
         uint32_t cnt = 0;
         TP_HIP(hipStreamSynchronize(st));
@@ -1080,6 +1145,22 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
     Device &d = device(dev);
     load_tune_file(d);
     Plan *p = nullptr;
+    if (capturing(st)) {
+        const Relaxed relaxed(true);
+        OwnStream ps;
+        TP_HIP(hipStreamCreateWithFlags(&ps.st, hipStreamNonBlocking));
+        rc = build_plan(d, rq, mode, ps.st, p);
+        if (rc) return rc;
+        TP_HIP(hipEventSynchronize(p->ready));
+        if (!p->captured) d.lru.erase(p->lru_pos);
+        p->captured = true;
+        Captured &c = d.captured[st];
+        Workspace *ws = nullptr;
+        rc = captured_workspace(c, ps.st, list_capacity(p->vtotal), ws);
+        if (rc) return rc;
+        TP_HIP(hipStreamSynchronize(ps.st));
+        return launch_plan(d, *p, resolve_tunings(d, *p, rq, prec, tuning), prec, mode, *ws, st, -1, nullptr, &c);
+    }
     rc = build_plan(d, rq, mode, st, p);
     if (rc) return rc;
     rc = begin_use(*p, st);
@@ -1128,9 +1209,7 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
     rc = get_workspace(d, st, list_capacity(p->vtotal), ws);
     if (rc) return rc;
     if (mail) *mail = take_mail();
-    // a captured launch may be replayed beside this stream's own calls: it counts
-    // directly
-    rc = launch_plan(d, *p, gtu, prec, mode, *ws, st, -1, mail ? *mail : nullptr, !capturing(st));
+    rc = launch_plan(d, *p, gtu, prec, mode, *ws, st, -1, mail ? *mail : nullptr);
     if (rc) {
         if (mail && *mail) give_mail(*mail);    // its kernel was not enqueued
         return rc;
@@ -1653,9 +1732,11 @@ int tp_release(void)
         }
         if (d.scratch_counts) hipFree(d.scratch_counts);
         for (auto &f : d.eflag) hipFree(f.second);
-        for (hipStream_t s2 : d.side) hipStreamDestroy(s2);
-        for (hipEvent_t e2 : d.join) hipEventDestroy(e2);
-        if (d.fork) hipEventDestroy(d.fork);
+        free_sides(d.sides);
+        for (auto &c : d.captured) {
+            for (Workspace &w : c.second.ws) hipFree(w.buf);
+            free_sides(c.second.sides);
+        }
     }
     g_dev.clear();
     collect_mail();

@@ -1,5 +1,5 @@
 """The host runtime's bookkeeping (csrc/tp_host.cpp on a HIP runtime of host memory, tests/host/runtime_harness.cpp):
-what a failed call leaves behind.  CPU only."""
+what a failed call leaves behind and what a captured call holds.  CPU only."""
 import ctypes
 import os
 import subprocess
@@ -162,3 +162,75 @@ def test_checked_call_refused_under_capture(hr):
     hr.fk_replay(g)
     assert a.holds(1)
     assert hr.tp_release() == 0 and hr.fk_blocks() == held
+
+
+def captured(hr, stream, calls):
+    """Graph of ``calls`` (functions of the stream) captured on it; launches recorded."""
+    n = hr.fk_launch_count()
+    hr.fk_begin(stream)
+    for call in calls:
+        assert call(stream) == 0
+    return hr.fk_end(stream), range(n, hr.fk_launch_count())
+
+
+def test_captured_call_beside_the_streams_own(hr):
+    """A captured call shares no memory that a launch writes with the stream's own calls, and what its graph points to
+    stays allocated and unchanged: after a larger own call has grown the stream's list, and after more new calls than
+    there are plans."""
+    a, st = Sample(50000), hr.fk_stream()
+    assert hr.tp_bin(*a.args(st)) == 0
+    own = hr.fk_launch_list(hr.fk_launch_count() - 1)
+    g, launches = captured(hr, st, [lambda s: hr.tp_bin(*a.args(s))])
+    assert [hr.fk_launch_list(i) for i in launches] != [own]
+    assert a.holds(1)
+    big = Sample(3000000, at=0x20000)
+    assert hr.tp_bin(*big.args(st)) == 0
+    for k in range(300):
+        b = Sample(900 + k, at=0x30000 + 0x100 * k)
+        assert hr.tp_bin(*b.args(st)) == 0
+    for i in launches:
+        assert hr.fk_live(hr.fk_launch_list(i)) and hr.fk_live(hr.fk_launch_samples(i))
+    for k in range(2, 5):
+        hr.fk_replay(g)
+        assert a.holds(k)
+    assert big.holds(1)
+
+
+def test_captured_without_a_call_before(hr):
+    """The first calls of all are captured, one of them several schemes on parallel branches, the second with a longer
+    list: nothing is recorded but kernels, and the replays and the stream's own calls count what they hold.  A second
+    graph of the stream takes no more memory."""
+    st = hr.fk_stream()
+    a = Sample(5000)
+    ss = [Sample(50000, PHI, 0x20000), Sample(200000, MASS, 0x30000)]
+    arr = batch(ss)
+    calls = [lambda s: hr.tp_bin(*a.args(s)), lambda s: hr.tp_batch(arr, 2, 1, None, 0, s),
+             lambda s: hr.tp_batch(arr, 2, 1, None, 1, s)]
+    g, _ = captured(hr, st, calls)
+    assert not any(s.counts.any() for s in [a] + ss)
+    for k in (1, 2):
+        hr.fk_replay(g)
+        assert a.holds(k) and all(s.holds(2 * k) for s in ss)
+    held = hr.fk_bytes()
+    g2, _ = captured(hr, st, calls)
+    assert hr.fk_bytes() == held
+    assert hr.tp_bin(*a.args(st)) == 0 and hr.tp_batch(arr, 2, 1, None, 1, None) == 0
+    hr.fk_replay(g2)
+    assert a.holds(4) and all(s.holds(7) for s in ss)
+
+
+def test_other_calls_while_a_capture_is_open(hr):
+    """A batch of several schemes on another stream while one is captured: the captured one's branches are its own."""
+    st, other = hr.fk_stream(), hr.fk_stream()
+    one = [Sample(50000, PHI, 0x20000), Sample(200000, MASS, 0x30000)]
+    two = [Sample(40000, PHI, 0x40000), Sample(300000, MASS, 0x50000)]
+    a1, a2 = batch(one), batch(two)
+    assert hr.tp_batch(a2, 2, 1, None, 0, other) == 0
+    n = hr.fk_launch_count()
+    hr.fk_begin(st)
+    assert hr.tp_batch(a1, 2, 1, None, 0, st) == 0
+    assert hr.tp_batch(a2, 2, 1, None, 0, other) == 0
+    g = hr.fk_end(st)
+    assert all(s.holds(2) for s in two) and hr.fk_launch_count() == n + 4
+    hr.fk_replay(g)
+    assert all(s.holds(1) for s in one) and all(s.holds(2) for s in two)
