@@ -312,7 +312,11 @@ int new_workspace(uint64_t cap, hipStream_t st, Workspace &w)
     w.xcount = reinterpret_cast<uint32_t *>(static_cast<char *>(w.buf) + cap * sizeof(uint64_t));
     w.xdone = w.xcount + 1;
     w.rep = reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(w.xcount) + 256);
-    TP_HIP(hipMemsetAsync(w.xcount, 0, COUNTER_BYTES, st));
+    const hipError_t e = hipMemsetAsync(w.xcount, 0, COUNTER_BYTES, st);
+    if (e != hipSuccess) {
+        hipFree(w.buf);
+        return hip_fail(TP_EHIP, std::string("clearing a workspace: ") + hipGetErrorString(e));
+    }
     return TP_OK;
 }
 
@@ -676,24 +680,30 @@ uint64_t plan_key(const std::vector<Req> &rq, int mode)
     return h;
 }
 
-// Release a plan and the graphs captured with it, once the work that reads
-// them has finished.
+void free_graph(GraphEntry &g)
+{
+    if (g.exec) hipGraphExecDestroy(g.exec);
+    if (g.graph) hipGraphDestroy(g.graph);
+    if (g.ws.buf) hipFree(g.ws.buf);
+    g = GraphEntry();
+}
+
+// Release a plan (also one whose upload failed) and the graphs captured with it,
+// once the work that reads them has finished.
 void free_plan(Device &d, Plan *q)
 {
-    hipEventSynchronize(q->ready);
+    if (q->ready) hipEventSynchronize(q->ready);
     if (q->used) hipEventSynchronize(q->last_use);
     for (uint64_t gk : q->graph_keys) {
         auto g = d.graphs.find(gk);
         if (g == d.graphs.end()) continue;
-        hipGraphExecDestroy(g->second.exec);
-        hipGraphDestroy(g->second.graph);
-        hipFree(g->second.ws.buf);
+        free_graph(g->second);
         d.graphs.erase(g);
     }
-    hipFree(q->dbuf);
-    hipHostFree(q->pinned);
-    hipEventDestroy(q->ready);
-    hipEventDestroy(q->last_use);
+    if (q->dbuf) hipFree(q->dbuf);
+    if (q->pinned) hipHostFree(q->pinned);
+    if (q->ready) hipEventDestroy(q->ready);
+    if (q->last_use) hipEventDestroy(q->last_use);
     delete q;
 }
 
@@ -711,6 +721,32 @@ int end_use(Plan &p, hipStream_t st)
     TP_HIP(hipEventRecord(p.last_use, st));
     p.last_stream = st;
     p.used = true;
+    return TP_OK;
+}
+
+// Device copies of a plan's tables, enqueued on ``st``.
+int upload_plan(Plan *p, hipStream_t st)
+{
+    if (p->hedges.empty()) p->hedges.push_back(0.0);
+    const size_t sb = p->hs.size() * sizeof(KSample);
+    const size_t eb = p->hedges.size() * sizeof(double);
+    const size_t fb = p->hfold.size() * sizeof(uint32_t);
+    const size_t eoff = (sb + 255) & ~size_t(255), foff = (eoff + eb + 255) & ~size_t(255);
+    const size_t tot = foff + fb;
+    if (hipMalloc(&p->dbuf, tot) != hipSuccess) return hip_fail(TP_ENOMEM, "plan table allocation failed");
+    if (hipHostMalloc(&p->pinned, tot, hipHostMallocDefault) != hipSuccess)
+        return hip_fail(TP_ENOMEM, "pinned staging allocation failed");
+    std::memcpy(p->pinned, p->hs.data(), sb);
+    std::memcpy(static_cast<char *>(p->pinned) + eoff, p->hedges.data(), eb);
+    if (fb) std::memcpy(static_cast<char *>(p->pinned) + foff, p->hfold.data(), fb);
+    p->dsamples = static_cast<KSample *>(p->dbuf);
+    p->dedges = reinterpret_cast<double *>(static_cast<char *>(p->dbuf) + eoff);
+    p->dfold = reinterpret_cast<uint32_t *>(static_cast<char *>(p->dbuf) + foff);
+    TP_HIP(hipMemcpyAsync(p->dbuf, p->pinned, tot, hipMemcpyHostToDevice, st));
+    TP_HIP(hipEventCreateWithFlags(&p->ready, hipEventDisableTiming));
+    TP_HIP(hipEventCreateWithFlags(&p->last_use, hipEventDisableTiming));
+    TP_HIP(hipEventRecord(p->ready, st));
+    p->made_on = st;
     return TP_OK;
 }
 
@@ -784,32 +820,13 @@ int build_plan(Device &d, const std::vector<Req> &rq, int mode, hipStream_t st, 
         return fail(TP_ERANGE, "too many samples once split at 2^32 bytes per array");
     }
     place_replicas(p->hs, p->hfold);
-    if (p->hedges.empty()) p->hedges.push_back(0.0);
-    const size_t sb = p->hs.size() * sizeof(KSample);
-    const size_t eb = p->hedges.size() * sizeof(double);
-    const size_t fb = p->hfold.size() * sizeof(uint32_t);
-    const size_t eoff = (sb + 255) & ~size_t(255), foff = (eoff + eb + 255) & ~size_t(255);
-    const size_t tot = foff + fb;
-    if (hipMalloc(&p->dbuf, tot) != hipSuccess) {
-        delete p;
-        return hip_fail(TP_ENOMEM, "plan table allocation failed");
+    const int rc = upload_plan(p, st);
+    if (rc) {
+        (void)hipStreamSynchronize(st);     // the copy may be under way
+        free_plan(d, p);
+        (void)hipGetLastError();
+        return rc;
     }
-    if (hipHostMalloc(&p->pinned, tot, hipHostMallocDefault) != hipSuccess) {
-        hipFree(p->dbuf);
-        delete p;
-        return hip_fail(TP_ENOMEM, "pinned staging allocation failed");
-    }
-    std::memcpy(p->pinned, p->hs.data(), sb);
-    std::memcpy(static_cast<char *>(p->pinned) + eoff, p->hedges.data(), eb);
-    if (fb) std::memcpy(static_cast<char *>(p->pinned) + foff, p->hfold.data(), fb);
-    p->dsamples = static_cast<KSample *>(p->dbuf);
-    p->dedges = reinterpret_cast<double *>(static_cast<char *>(p->dbuf) + eoff);
-    p->dfold = reinterpret_cast<uint32_t *>(static_cast<char *>(p->dbuf) + foff);
-    TP_HIP(hipMemcpyAsync(p->dbuf, p->pinned, tot, hipMemcpyHostToDevice, st));
-    TP_HIP(hipEventCreateWithFlags(&p->ready, hipEventDisableTiming));
-    TP_HIP(hipEventCreateWithFlags(&p->last_use, hipEventDisableTiming));
-    TP_HIP(hipEventRecord(p->ready, st));
-    p->made_on = st;
     d.plans[key] = p;
     p->lru_pos = d.lru.insert(d.lru.end(), key);
     if (d.lru.size() > MAX_PLANS) {
@@ -1133,6 +1150,30 @@ int current_device(int &id)
     return TP_OK;
 }
 
+// A graph of the plan's launch, with a workspace of its own.
+int make_graph(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int prec, int mode, hipStream_t st,
+               GraphEntry &ge)
+{
+    int rc = new_workspace(list_capacity(p.vtotal), st, ge.ws);
+    if (rc) return rc;
+    TP_HIP(hipStreamSynchronize(st));
+    OwnStream cap;
+    TP_HIP(hipStreamCreateWithFlags(&cap.st, hipStreamNonBlocking));
+    TP_HIP(hipStreamWaitEvent(cap.st, p.ready, 0));
+    TP_HIP(hipStreamSynchronize(cap.st));
+    TP_HIP(hipStreamBeginCapture(cap.st, hipStreamCaptureModeThreadLocal));
+    const bool was_on = g_timing.on;
+    g_timing.on = false;
+    rc = launch_plan(d, p, gtu, prec, mode, ge.ws, cap.st);
+    const hipError_t e = hipStreamEndCapture(cap.st, &ge.graph);
+    g_timing.on = was_on;
+    if (e != hipSuccess) (void)hipGetLastError();
+    if (rc) return rc;
+    if (e != hipSuccess) return fail(TP_EHIP, std::string("graph capture: ") + hipGetErrorString(e));
+    TP_HIP(hipGraphInstantiate(&ge.exec, ge.graph, nullptr, nullptr, 0));
+    return TP_OK;
+}
+
 // ``mail`` (one request only): gets a host word that holds stats->n_unresolved
 // once the launch has ended, or null; of no use to the caller on an error.
 int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning, int flags, hipStream_t st,
@@ -1173,25 +1214,11 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
         auto it = d.graphs.find(gk);
         if (it == d.graphs.end()) {
             GraphEntry ge;
-            rc = new_workspace(list_capacity(p->vtotal), st, ge.ws);
-            if (rc) return rc;
-            TP_HIP(hipStreamSynchronize(st));
-            hipStream_t cap;
-            TP_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-            TP_HIP(hipStreamWaitEvent(cap, p->ready, 0));
-            TP_HIP(hipStreamSynchronize(cap));
-            const bool was_on = g_timing.on;
-            g_timing.on = false;
-            TP_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-            rc = launch_plan(d, *p, gtu, prec, mode, ge.ws, cap);
-            hipGraph_t g = nullptr;
-            hipError_t ee = hipStreamEndCapture(cap, &g);
-            g_timing.on = was_on;
-            hipStreamDestroy(cap);
-            if (rc) return rc;
-            if (ee != hipSuccess) return hip_fail(TP_EHIP, std::string("graph capture: ") + hipGetErrorString(ee));
-            ge.graph = g;
-            TP_HIP(hipGraphInstantiate(&ge.exec, g, nullptr, nullptr, 0));
+            rc = make_graph(d, *p, gtu, prec, mode, st, ge);
+            if (rc) {
+                free_graph(ge);
+                return rc;
+            }
             it = d.graphs.emplace(gk, ge).first;
             p->graph_keys.push_back(gk);
         }
@@ -1725,11 +1752,7 @@ int tp_release(void)
         Device &d = kv.second;
         for (auto &w : d.ws) hipFree(w.second.buf);
         for (auto &p : d.plans) free_plan(d, p.second);
-        for (auto &g : d.graphs) {
-            hipGraphExecDestroy(g.second.exec);
-            hipGraphDestroy(g.second.graph);
-            hipFree(g.second.ws.buf);
-        }
+        for (auto &g : d.graphs) free_graph(g.second);
         if (d.scratch_counts) hipFree(d.scratch_counts);
         for (auto &f : d.eflag) hipFree(f.second);
         free_sides(d.sides);

@@ -41,7 +41,7 @@ def hr(built):
     yield built
     built.fk_fail(b"", 0)
     built.fk_pending()
-    assert built.tp_release() == 0
+    assert built.tp_release() == 0 and built.fk_blocks() == 0
 
 
 class Sample:
@@ -132,7 +132,7 @@ def test_failed_tuning_leaves_no_counts(hr):
 def test_failed_checked_calls_keep_no_host_word(hr, name):
     """40 checked calls that fail, more than there are host words: the next one still gets its count through one, and
     tp_release gives their page back."""
-    a, un, held = Sample(5000), ctypes.c_uint64(), hr.fk_blocks()
+    a, un = Sample(5000), ctypes.c_uint64()
     assert hr.tp_bin_checked(*a.args(), ctypes.byref(un)) == 0
     for k in range(40):
         b = Sample(5000 + k, at=0x20000 + 0x100 * k) if name == "hipMalloc" else a
@@ -145,13 +145,13 @@ def test_failed_checked_calls_keep_no_host_word(hr, name):
     assert hr.tp_bin_checked(*a.args(), ctypes.byref(un)) == 0
     hr.fk_fail(b"", 0)
     assert un.value == 3 and a.holds(1)
-    assert hr.tp_release() == 0 and hr.fk_blocks() == held
+    assert hr.tp_release() == 0 and hr.fk_blocks() == 0
 
 
 def test_checked_call_refused_under_capture(hr):
     """A checked call waits for its stream, which cannot be waited for while it is captured: refused with nothing
     recorded and no host word taken."""
-    a, un, st, held = Sample(5000), ctypes.c_uint64(), hr.fk_stream(), hr.fk_blocks()
+    a, un, st = Sample(5000), ctypes.c_uint64(), hr.fk_stream()
     assert hr.tp_bin_checked(*a.args(st), ctypes.byref(un)) == 0
     n = hr.fk_launch_count()
     hr.fk_begin(st)
@@ -161,7 +161,7 @@ def test_checked_call_refused_under_capture(hr):
     g = hr.fk_end(st)
     hr.fk_replay(g)
     assert a.holds(1)
-    assert hr.tp_release() == 0 and hr.fk_blocks() == held
+    assert hr.tp_release() == 0 and hr.fk_blocks() == 0
 
 
 def captured(hr, stream, calls):
@@ -234,3 +234,37 @@ def test_other_calls_while_a_capture_is_open(hr):
     assert all(s.holds(2) for s in two) and hr.fk_launch_count() == n + 4
     hr.fk_replay(g)
     assert all(s.holds(1) for s in one) and all(s.holds(2) for s in two)
+
+
+@pytest.mark.parametrize("name", ["hipMalloc", "hipHostMalloc", "hipMemcpyAsync", "hipMemsetAsync", "hipEventCreateWithFlags",
+                                  "hipEventRecord", "hipStreamSynchronize", "hipStreamCreateWithFlags", "hipStreamWaitEvent",
+                                  "hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate", "hipGraphLaunch",
+                                  "launch_pass", "launch_exact"])
+@pytest.mark.parametrize("flags,under_capture", [(0, False), (1, False), (0, True)])
+def test_failed_calls_lose_no_memory(hr, name, flags, under_capture):
+    """A first batch of two schemes whose k-th call of one function fails, for every k that it reaches: tp_release gives
+    everything back (the fixture looks), and the batch then counts what it holds."""
+    ss = [Sample(50000, PHI), Sample(200000, MASS, 0x20000)]
+    arr, rc = batch(ss), 1
+    for k in range(1, 20):
+        assert hr.tp_release() == 0 and hr.fk_blocks() == 0, k
+        for s in ss:
+            s.clear()
+        st = hr.fk_stream() if under_capture else None
+        if under_capture:
+            hr.fk_begin(st)
+        hr.fk_fail(name.encode(), k)
+        rc = hr.tp_batch(arr, 2, 1, None, flags, st)
+        hr.fk_fail(b"", 0)
+        if under_capture:
+            g = hr.fk_end(st)
+        if rc == 0:
+            break
+        for s in ss:
+            s.clear()
+        assert hr.tp_batch(arr, 2, 1, None, flags, None) == 0
+        assert all(s.holds(1) for s in ss), k
+    assert rc == 0
+    if under_capture:
+        hr.fk_replay(g)
+    assert all(s.holds(1) for s in ss)
