@@ -91,12 +91,15 @@ struct Workspace {
     uint32_t *xdone = nullptr;
     uint64_t *rep = nullptr;   // replicated counters
     uint64_t cap = 0;      // list entries
+    int64_t rep_cap = 0;   // words of replicated counters
     // A launch over this workspace was begun and its exact-tier kernel, which leaves
     // the list and the replicas empty, not enqueued: they may hold that launch's events.
     bool dirty = false;
 };
 
-constexpr size_t COUNTER_BYTES = 256 + REP_WORDS * sizeof(uint64_t);   // list counters and replicas
+// Bytes of a workspace's list counters and replicas, which are clear between launches.
+size_t counter_bytes(int64_t rep) { return 256 + (size_t)rep * sizeof(uint64_t); }
+constexpr int64_t REP_MIN = int64_t(1) << 14;    // words of a stream's replicas: one sample of up to 125 bins
 
 // List capacity for a launch over ``vtotal`` virtual events.
 uint64_t list_capacity(int64_t vtotal)
@@ -128,6 +131,7 @@ struct Plan {
     hipStream_t made_on = nullptr;
     KSample *dsamples = nullptr;
     double *dedges = nullptr;
+    int64_t rep_used = 0;        // words of replicated counters
     std::vector<uint32_t> hfold; // work items of the counter fold
     uint32_t *dfold = nullptr;
     // the latest enqueued work that reads the plan (a use on another stream
@@ -302,17 +306,19 @@ struct OwnStream {
     }
 };
 
-// A deferral workspace of ``cap`` list entries; its counters are cleared on ``st``.
-int new_workspace(uint64_t cap, hipStream_t st, Workspace &w)
+// A workspace of ``cap`` list entries and ``rep`` words of replicated counters; its
+// counters are cleared on ``st``.
+int new_workspace(uint64_t cap, int64_t rep, hipStream_t st, Workspace &w)
 {
-    const size_t bytes = cap * sizeof(uint64_t) + COUNTER_BYTES;
+    const size_t bytes = cap * sizeof(uint64_t) + counter_bytes(rep);
     if (hipMalloc(&w.buf, bytes) != hipSuccess) return hip_fail(TP_ENOMEM, "workspace allocation failed");
     w.cap = cap;
+    w.rep_cap = rep;
     w.xlist = static_cast<uint64_t *>(w.buf);
     w.xcount = reinterpret_cast<uint32_t *>(static_cast<char *>(w.buf) + cap * sizeof(uint64_t));
     w.xdone = w.xcount + 1;
     w.rep = reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(w.xcount) + 256);
-    const hipError_t e = hipMemsetAsync(w.xcount, 0, COUNTER_BYTES, st);
+    const hipError_t e = hipMemsetAsync(w.xcount, 0, counter_bytes(rep), st);
     if (e != hipSuccess) {
         hipFree(w.buf);
         return hip_fail(TP_EHIP, std::string("clearing a workspace: ") + hipGetErrorString(e));
@@ -321,27 +327,31 @@ int new_workspace(uint64_t cap, hipStream_t st, Workspace &w)
 }
 
 // The stream's workspace, grown (after the stream's earlier work) to ``cap`` entries
-// and cleared if a failed launch left it dirty.
-int get_workspace(Device &d, hipStream_t st, uint64_t cap, Workspace *&out)
+// and ``rep`` words and cleared if a failed launch left it dirty.
+int get_workspace(Device &d, hipStream_t st, uint64_t cap, int64_t rep, Workspace *&out)
 {
     auto it = d.ws.find(st);
     if (it != d.ws.end() && it->second.dirty) {
         // the failed launch's side branches may not have been joined
         for (hipStream_t s2 : d.sides.side) TP_HIP(hipStreamSynchronize(s2));
-        TP_HIP(hipMemsetAsync(it->second.xcount, 0, COUNTER_BYTES, st));
+        TP_HIP(hipMemsetAsync(it->second.xcount, 0, counter_bytes(it->second.rep_cap), st));
         it->second.dirty = false;
     }
-    if (it != d.ws.end() && it->second.cap >= cap) {
+    if (it != d.ws.end() && it->second.cap >= cap && it->second.rep_cap >= rep) {
         out = &it->second;
         return TP_OK;
     }
+    int64_t words = REP_MIN;
+    while (words < rep) words *= 2;
     if (it != d.ws.end()) {
+        cap = std::max(cap, it->second.cap);
+        words = std::max(words, it->second.rep_cap);
         TP_HIP(hipStreamSynchronize(st));
         hipFree(it->second.buf);
         d.ws.erase(it);
     }
     Workspace w;
-    const int rc = new_workspace(cap, st, w);
+    const int rc = new_workspace(cap, words, st, w);
     if (rc) return rc;
     out = &(d.ws[st] = w);
     return TP_OK;
@@ -354,7 +364,7 @@ int captured_workspace(Captured &c, hipStream_t ps, uint64_t cap, Workspace *&ou
         uint64_t pow2 = XCAP_MIN;
         while (pow2 < cap) pow2 *= 2;
         Workspace w;
-        const int rc = new_workspace(pow2, ps, w);
+        const int rc = new_workspace(pow2, 0, ps, w);
         if (rc) return rc;
         c.ws.push_back(w);
     }
@@ -637,14 +647,16 @@ void place_replica(KSample &k, int64_t &used)
 
 int fold_items(const KSample &k) { return k.rep_off < 0 ? 0 : (rep_words(k.nbtot) + FOLD - 1) / FOLD; }
 
-// Replicas of every sample of a plan and the work items of their fold.
-void place_replicas(std::vector<KSample> &hs, std::vector<uint32_t> &fold)
+// Replicas of every sample of a plan and the work items of their fold; the words
+// they take.
+int64_t place_replicas(std::vector<KSample> &hs, std::vector<uint32_t> &fold)
 {
     int64_t used = 0;
     for (size_t s = 0; s < hs.size(); ++s) {
         place_replica(hs[s], used);
         for (int i = 0; i < fold_items(hs[s]); ++i) fold.push_back((uint32_t)(s << 8) | (uint32_t)i);
     }
+    return used;
 }
 static_assert((rep_words(MAXBINS) + FOLD - 1) / FOLD <= 256, "the fold's item index has 8 bits");
 static_assert(MAXREP * rep_stride(MAXBINS) <= REP_WORDS, "one sample's replicas always fit");
@@ -819,7 +831,7 @@ int build_plan(Device &d, const std::vector<Req> &rq, int mode, hipStream_t st, 
         delete p;
         return fail(TP_ERANGE, "too many samples once split at 2^32 bytes per array");
     }
-    place_replicas(p->hs, p->hfold);
+    p->rep_used = place_replicas(p->hs, p->hfold);
     const int rc = upload_plan(p, st);
     if (rc) {
         (void)hipStreamSynchronize(st);     // the copy may be under way
@@ -1154,7 +1166,7 @@ int current_device(int &id)
 int make_graph(Device &d, const Plan &p, const std::vector<tp_tuning> &gtu, int prec, int mode, hipStream_t st,
                GraphEntry &ge)
 {
-    int rc = new_workspace(list_capacity(p.vtotal), st, ge.ws);
+    int rc = new_workspace(list_capacity(p.vtotal), p.rep_used, st, ge.ws);
     if (rc) return rc;
     TP_HIP(hipStreamSynchronize(st));
     OwnStream cap;
@@ -1233,7 +1245,7 @@ int run(const std::vector<Req> &rq, int prec, int mode, const tp_tuning *tuning,
         return end_use(*p, st);
     }
     Workspace *ws = nullptr;
-    rc = get_workspace(d, st, list_capacity(p->vtotal), ws);
+    rc = get_workspace(d, st, list_capacity(p->vtotal), p->rep_used, ws);
     if (rc) return rc;
     if (mail) *mail = take_mail();
     rc = launch_plan(d, *p, gtu, prec, mode, *ws, st, -1, mail ? *mail : nullptr);
@@ -1567,7 +1579,7 @@ int tp_autotune(const tp_sample *samples, int32_t nsamples, int32_t precision, v
     Workspace *ws = nullptr;
     rc = build_plan(d, rq, 0, st, p);
     if (!rc) rc = begin_use(*p, st);
-    if (!rc) rc = get_workspace(d, st, list_capacity(p->vtotal), ws);
+    if (!rc) rc = get_workspace(d, st, list_capacity(p->vtotal), p->rep_used, ws);
     // time ``trials`` runs of ``reps`` launches of group g with shape t; best run, ms per launch
     auto measure = [&](size_t g, const tp_tuning &t, int trials, int reps, float &ms) -> int {
         const std::vector<tp_tuning> gtu(p->groups.size(), t);

@@ -52,7 +52,7 @@ struct KSample {
 // copies into the counters and leaves them zero for the next launch.  One copy
 // holds the (nbtot + 1) * 4 counts, then the NSTAT statistics.
 enum { MAXREP = 32, REP_EVENTS = 4096 };      // a copy for every REP_EVENTS events, up to MAXREP
-constexpr int64_t REP_WORDS = int64_t(1) << 19;     // words of a workspace's replica array (4 MiB)
+constexpr int64_t REP_WORDS = int64_t(1) << 19;     // words, at most, of a launch's replica array (4 MiB)
 constexpr int FOLD = 64;                      // counters per work item of the fold
 constexpr int rep_words(int nbtot) { return (nbtot + 1) * 4 + NSTAT; }
 constexpr int rep_stride(int nbtot) { return (rep_words(nbtot) + 15) & ~15; }   // whole 128-byte lines

@@ -268,3 +268,29 @@ def test_failed_calls_lose_no_memory(hr, name, flags, under_capture):
     if under_capture:
         hr.fk_replay(g)
     assert all(s.holds(1) for s in ss)
+
+
+WIDE = [synth.mass_axis((0, 1), 900.0, 1800.0, 32), synth.mass_axis((2, 3), 200.0, 900.0, 32)]
+
+
+def test_workspaces_take_what_their_launches_need(hr):
+    """List entries (2^16 at least, 8 B each) and, from 16385 events on, replicated counters: 32 copies of 4108 + 8
+    counters for 1024 bins.  Streams and graphs of small samples hold no more than their lists and 2^14 words."""
+    small = Sample(1000)
+    streams = [hr.fk_stream() for _ in range(8)]
+    for st in streams:
+        assert hr.tp_bin(*small.args(st)) == 0
+    assert hr.fk_bytes() < 8 * (2 ** 16 + 2 ** 14 + 64) * 8 + 10000
+    held = hr.fk_bytes()
+    for k in range(8):
+        assert hr.tp_batch(batch([Sample(2000 + k)]), 1, 1, None, 1, None) == 0
+    assert hr.fk_bytes() - held < 8 * (2 ** 16 + 64) * 8 + 80000
+    held = hr.fk_bytes()
+    wide = [Sample(130000, WIDE, 0x20000 + 0x1000 * k) for k in range(6)]
+    for k, s in enumerate(wide):                    # the stream's workspace grows, by replicas and by list
+        assert hr.tp_bin(*s.args(streams[0])) == 0 and hr.tp_bin(*small.args(streams[0])) == 0
+    assert hr.fk_bytes() - held < (2 ** 17 + 2 ** 18) * 8 + 300000
+    arr = batch(wide)
+    for flags in (0, 1, 1):
+        assert hr.tp_batch(arr, 6, 1, None, flags, streams[0]) == 0
+    assert all(s.holds(4) for s in wide) and small.holds(14)
