@@ -955,7 +955,9 @@ hipError_t launch_ntd(const EParams &p, hipStream_t st)
     // and parts (S), the number of parts chosen for full rounds of resident
     // workgroups: at 3e5 events the L2 misses fall from 72 to 2 % of the
     // requests, the time from 19.9 to 19.5 ms.  A smaller one (or one with too
-    // few pairs for that) is split evenly, in up to 16 full rounds.
+    // few pairs for that) is split evenly, in up to 16 full rounds.  The rounds of
+    // a split by parts are of RESIDENT workgroups at every width (measured at 128
+    // columns only; three fit a compute unit at 32 and 64, see below).
     const int64_t total = nb * (nb + 1) / 2;
     int64_t S = 0, grid = total / 64;
     if (p.n * (p.C + 4 * p.D) > L2_BYTES && pairs * 2 > RESIDENT) {
