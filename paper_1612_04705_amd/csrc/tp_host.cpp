@@ -71,7 +71,7 @@ int exact_grid(int64_t vtotal, int nfold)
 {
     return (int)std::min<int64_t>(EXACT_GRID, std::max<int64_t>(std::max(16, nfold), vtotal >> 16));
 }
-constexpr size_t MAX_PLANS = 256;        // launch plans kept per device
+constexpr size_t MAX_PLANS = 256;        // launch plans kept per device, beside those that callers' graphs point to
 constexpr size_t LDS_LIMIT = 64 * 1024;
 
 uint64_t fnv(const void *p, size_t n, uint64_t h = 1469598103934665603ull)
@@ -281,8 +281,8 @@ bool capturing(hipStream_t st)
     return false;
 }
 
-// While a stream is being captured the thread may not allocate or wait, unless its
-// capture mode is relaxed.
+// While a stream is being captured a thread may not allocate or wait (the call is
+// refused and the capture spoilt) unless the thread's capture mode is relaxed.
 struct Relaxed {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     const bool on;
@@ -341,6 +341,7 @@ int get_workspace(Device &d, hipStream_t st, uint64_t cap, int64_t rep, Workspac
         out = &it->second;
         return TP_OK;
     }
+    const Relaxed relaxed(true);        // another stream may be under capture
     int64_t words = REP_MIN;
     while (words < rep) words *= 2;
     if (it != d.ws.end()) {
@@ -1391,7 +1392,7 @@ int tp_bin_checked(const tp_events *ev, const tp_channel *ch, const tp_binning *
         if (e == hipSuccess) give_mail(mail);
         else g_mail_owed.push_back(mail);
     }
-    TP_HIP(e);
+    if (e != hipSuccess) return hip_fail(TP_EHIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(e));
     if (!mail) TP_HIP(hipMemcpy(unresolved, &stats->n_unresolved, sizeof *unresolved, hipMemcpyDeviceToHost));
     return TP_OK;
 }

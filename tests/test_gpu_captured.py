@@ -90,3 +90,23 @@ def test_captured_batch_of_schemes(tp):
         b.run(tp.TP_PREC_F32_RECHECK, graph=k > 0, check=True)
         passes += 1
         assert all(p.holds(passes) for p in parts), (k, passes)
+
+
+def test_own_call_grows_its_stream_while_another_is_captured(tp):
+    """A call whose tables are there grows its stream's memory during the capture of another stream, which goes on."""
+    wide = Part(tp, [synth.mass_axis((0, 1), 1900.0, 5100.0, 32), synth.mass_axis((2, 3), 900.0, 4200.0, 32)], 140001, 99, None)
+    few = Part(tp, SCHEMES[1], 500, 98, None)
+    st, here, there = (torch.cuda.Stream() for _ in range(3))
+    x = torch.zeros(8, device="cuda")
+    torch.cuda.synchronize()
+    wide.bin(tp, stream=there, check=False)
+    few.bin(tp, stream=here, check=False)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        x.add_(1)
+        wide.bin(tp, stream=here, check=False)
+        few.bin(tp, check=False)
+    g.replay()
+    torch.cuda.synchronize()
+    assert wide.holds(2) and few.holds(2) and x.tolist() == [1.0] * 8

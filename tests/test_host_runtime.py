@@ -294,3 +294,15 @@ def test_workspaces_take_what_their_launches_need(hr):
     for flags in (0, 1, 1):
         assert hr.tp_batch(arr, 6, 1, None, flags, streams[0]) == 0
     assert all(s.holds(4) for s in wide) and small.holds(14)
+
+
+def test_workspace_grows_while_another_stream_is_captured(hr):
+    """A sample whose tables are there, on a stream whose workspace is too small for its replicas or its list, while
+    another stream is captured: the workspace grows and the capture is not disturbed."""
+    small, wide, long = Sample(1000), Sample(50000, WIDE, 0x20000), Sample(300000, at=0x30000)
+    st, here, there = (hr.fk_stream() for _ in range(3))
+    assert hr.tp_bin(*wide.args(there)) == 0 and hr.tp_bin(*long.args(there)) == 0 and hr.tp_bin(*small.args(here)) == 0
+    hr.fk_begin(st)
+    assert hr.tp_bin(*wide.args(here)) == 0 and hr.tp_bin(*long.args(here)) == 0
+    hr.fk_end(st)
+    assert wide.holds(2) and long.holds(2) and hr.fk_pending() == 0
