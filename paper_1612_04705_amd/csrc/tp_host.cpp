@@ -321,6 +321,7 @@ int new_workspace(uint64_t cap, int64_t rep, hipStream_t st, Workspace &w)
     const hipError_t e = hipMemsetAsync(w.xcount, 0, counter_bytes(rep), st);
     if (e != hipSuccess) {
         hipFree(w.buf);
+        w = Workspace();
         return hip_fail(TP_EHIP, std::string("clearing a workspace: ") + hipGetErrorString(e));
     }
     return TP_OK;

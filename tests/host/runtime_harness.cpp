@@ -29,6 +29,7 @@ std::string fk_name;            // the next calls of this function: the fk_after
 int fk_after = 0;
 std::map<void *, size_t> fk_alloc;
 size_t fk_pinned = 0;
+int fk_wrong = 0;               // frees of what is not allocated
 int fk_captures = 0;            // captures under way
 hipStreamCaptureMode fk_mode = hipStreamCaptureModeGlobal;
 std::vector<KParams> fk_launches;
@@ -84,7 +85,10 @@ hipError_t hipFree(void *p)
 {
     if (!p) return hipSuccess;
     FK_UNSAFE(hipFree);
-    if (!fk_alloc.erase(p)) return ret(hipErrorInvalidValue);
+    if (!fk_alloc.erase(p)) {
+        ++fk_wrong;
+        return ret(hipErrorInvalidValue);
+    }
     std::free(p);
     return hipSuccess;
 }
@@ -247,6 +251,7 @@ int64_t fk_bytes()
     for (auto &a : fk_alloc) n += a.second;
     return (int64_t)n;
 }
+int fk_wrong_frees() { return fk_wrong; }
 int64_t fk_blocks() { return (int64_t)(fk_alloc.size() + fk_pinned); }
 // Whether a block of device memory that starts at or holds p is allocated.
 int fk_live(const void *p)

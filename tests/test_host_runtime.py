@@ -41,7 +41,7 @@ def hr(built):
     yield built
     built.fk_fail(b"", 0)
     built.fk_pending()
-    assert built.tp_release() == 0 and built.fk_blocks() == 0
+    assert built.tp_release() == 0 and built.fk_blocks() == 0 and built.fk_wrong_frees() == 0
 
 
 class Sample:
