@@ -334,6 +334,7 @@ int get_workspace(Device &d, hipStream_t st, uint64_t cap, int64_t rep, Workspac
     auto it = d.ws.find(st);
     if (it != d.ws.end() && it->second.dirty) {
         // the failed launch's side branches may not have been joined
+        const Relaxed relaxed(true);    // another stream may be under capture
         for (hipStream_t s2 : d.sides.side) TP_HIP(hipStreamSynchronize(s2));
         TP_HIP(hipMemsetAsync(it->second.xcount, 0, counter_bytes(it->second.rep_cap), st));
         it->second.dirty = false;

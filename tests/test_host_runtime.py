@@ -306,3 +306,18 @@ def test_workspace_grows_while_another_stream_is_captured(hr):
     assert hr.tp_bin(*wide.args(here)) == 0 and hr.tp_bin(*long.args(here)) == 0
     hr.fk_end(st)
     assert wide.holds(2) and long.holds(2) and hr.fk_pending() == 0
+
+
+def test_cleared_while_another_stream_is_captured(hr):
+    """The call after a failed one, while another stream is captured."""
+    ss = [Sample(50000, PHI), Sample(200000, MASS, 0x20000)]
+    arr, st, here = batch(ss), hr.fk_stream(), hr.fk_stream()
+    hr.fk_fail(b"launch_exact", 1)
+    assert hr.tp_batch(arr, 2, 1, None, 0, here) != 0
+    hr.fk_fail(b"", 0)
+    for s in ss:
+        s.clear()
+    hr.fk_begin(st)
+    assert hr.tp_batch(arr, 2, 1, None, 0, here) == 0
+    hr.fk_end(st)
+    assert all(s.holds(1) for s in ss)
