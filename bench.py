@@ -232,7 +232,8 @@ def energy_leg(n, nperm, dev, per_pass=126, cpu_events=0):
             "launches": len(ks), "seconds": sec, "seconds_per_pass": sec / len(ks),
             "ms_per_permutation": sec * 1e3 / nperm,
             "unordered_pairs_per_s": pairs * len(ks) / sec,
-            "roofline": {"bound": "mfma" if t_mfma >= t_valu else "alu", "achieved": npairs / sec / 1e12, "peak": npairs / t_bound / 1e12,
+            "roofline": {"bound": "mfma" if t_mfma >= t_valu else "alu",
+                         "achieved": npairs / sec / 1e12, "peak": npairs / t_bound / 1e12,
                          "unit": "Tpair/s", "frac": t_bound / sec, "unit_times_sum_over_time": (t_mfma + t_valu) / sec,
                          "per_pair": {"mfma_f16_flops_distance": 64, "mfma_f16_flops_columns": 4 * C0,
                                       "valu_lane_ops": 3},
